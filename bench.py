@@ -37,17 +37,19 @@ BYTES_UPDATE_18 = 4 * 144 * 2 + 128  # update with 18-real links: R+W 4 x 144 B,
 BYTES_UPDATE_8 = 4 * 64 * 2 + 128  # update with 8-real links: R+W 4 x 64 B, R+W 64 B
 BYTES_UPDATE_SU2 = 4 * 32 * 2 + 32 * 2  # SU(2) update: R+W 4 links x 32 B, R+W 2 fields
 SD_TOL = 1e-10  # plain steepest descent needs thousands of sweeps at 32^4
-# algorithmic bytes per site of each sweep kernel: FP64, and the FP32 sweeps
-# of a mixed solve, whose last transform pass also does G <- g G (R field 32,
-# R+W G 96, the field itself not written back) and whose update forms the
-# links from the input copy U0 (R U0 192, R G 48, W field 32).  Where the
+# algorithmic bytes per site of each sweep kernel: FP64 sweeps (12-real links,
+# 49152 sites or more) and the FP32 sweeps of a mixed solve, whose last
+# transform pass also does G <- g G (FP64: R field 64, R+W G 192, the field
+# itself not written back) and whose update forms the links from the input
+# links U0 (FP64: R U0 384, R G 96, W field 64).  Where the
 # planes of all four fields do not fit one block (fp32_acc_fused), the
 # accumulation is a kernel of its own after a plain inverse pass (64 + 32 + 96).
 BYTES_PER_SITE = {
-    "fp64": {"fft_xy_fwd": 128, "fft_zt": 128, "fft_xy_inv": 128, "update": 896, "finalize": 0},
+    "fp64": {"fft_xy_fwd": 128, "fft_zt": 128, "fft_xy_inv": 256, "update": 544, "finalize": 0},
     "fp32": {"fft_xy_fwd": 64, "fft_zt": 64, "fft_xy_inv": 128, "update": 272, "finalize": 0},
 }
 BYTES_XY_INV_ACC_SEPARATE = 64 + 32 + 96
+BYTES_XY_INV_ACC_SEPARATE_64 = 128 + 64 + 192
 # differentiation kernels, algorithmic bytes per site: dF/domega reads the
 # divergence of the rotated links (64) and omega (64) and writes the gradient
 # (64); dtheta/deps reads the 12-real links (384), Delta (64; neighbours
@@ -271,6 +273,10 @@ def main() -> int:
     if not fp32_acc_fused(Lrun):
         fp32_bytes["fft_xy_inv"] = BYTES_XY_INV_ACC_SEPARATE
     fp64_bytes = dict(BYTES_PER_SITE["fp64"])
+    if args.link_format != 12:
+        fp64_bytes["fft_xy_inv"] = 128  # the other link formats store their links
+    elif max(Lrun) > 32:
+        fp64_bytes["fft_xy_inv"] = BYTES_XY_INV_ACC_SEPARATE_64
     fp64_bytes["update"] = {12: fp64_bytes["update"], 18: BYTES_UPDATE_18,
                             8: BYTES_UPDATE_8}[args.link_format]
     for name, prof, nbytes in (("fp64", prof64, fp64_bytes), ("fp32", prof32, fp32_bytes)):
@@ -291,7 +297,7 @@ def main() -> int:
         log(f"reference copy: {U0.numel() * 16} bytes read and written")
         print(json.dumps({"value": round(ips, 2), "unit": "iters/s", "per_kernel": per_kernel,
                           "overhead": overhead, "roofline_update_GBps": round(achieved, 1),
-                          "sweep_GBps": round(1280 * V * ips / 1e9, 1),
+                          "sweep_GBps": round(sum(fp64_bytes.values()) * V * ips / 1e9, 1),
                           "copy_bytes": U0.numel() * 16}), flush=True)
         return 0
 
@@ -449,7 +455,7 @@ def main() -> int:
             "per_kernel_ms": {k: round(v, 4) for k, v in prof48.items()},
             "update_GBps": round(BYTES_PER_SITE["fp64"]["update"] * V48 /
                                  (prof48["update"] * 1e-3) / 1e9, 1),
-            "sweep_GBps": round(1280 * V48 * ips48 / 1e9, 1),
+            "sweep_GBps": round((256 + BYTES_XY_INV_ACC_SEPARATE_64 + 544) * V48 * ips48 / 1e9, 1),
             "per_call_ms": round(1e3 * ss48["t_0"], 3)}
         log(f"48^3x96: {variants['48^3x96/fp64']}")
         g48 = None
@@ -551,9 +557,10 @@ def main() -> int:
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                      "traffic": measured_traffic(),
-                     "kernel": "k_update<double> (update + next divergence)",
+                     "kernel": "k_update_u0<double> (links from U0 and G, next divergence)",
                      "bytes_per_site": BYTES_PER_SITE["fp64"]["update"]},
-        "sweep_roofline_frac": round(1280 * V * ips / 1e9 / HBM_PEAK_GBS, 4),
+        "sweep_roofline_frac": round(sum(BYTES_PER_SITE["fp64"].values()) * V * ips / 1e9 /
+                                     HBM_PEAK_GBS, 4),
         "cpu_baseline": cpu,
         "time_to_theta_ms": {"fp64": t64, "mixed": tmx, "speedup_mixed": round(t64 / tmx, 3)},
         "solves": solves,

@@ -44,7 +44,7 @@ struct lgf_ctx {
     double theta_switch = 1e-8;
     bool accelerate = true;  // false: plain steepest descent (no transform)
     bool exact_exp = false;  // true: g = exp((alpha/2) L Delta) exactly
-    double half_alpha = 0;   // alpha/2 of the sweeps being enqueued (FP64 G accumulation)
+    double half_alpha = 0;   // alpha/2 of the sweeps being enqueued (G accumulation)
 
     // working links (SoA; 12-real by default, 18-real or SU(2) row 0 by the
     // context's format): FP64 double buffer; the FP32 pair aliases L64[1]
@@ -187,6 +187,11 @@ template <> struct prec<float> {
 // SU(2) updates G32 in place.
 float2 *acc_G(lgf_ctx *c, int n) { return (c->g.nc == 3 && (n & 1)) ? c->L32[1] : c->G32; }
 
+// The FP64 transformation after n sweeps of a phase that keeps U0 (in L64[0])
+// and G: the two buffers lie in the second link buffer, which such a phase
+// does not need (after a hand-over the FP32 copies there are dead).
+double2 *acc_G64(lgf_ctx *c, int n) { return c->L64[1] + (n & 1) * 6 * c->g.S; }
+
 // Arguments of launch_update for the sweep from buffer `cur` into `cur^1`.
 template <class T>
 hipError_t sweep_update(lgf_ctx *c, int cur, void *D, T half_alpha, const fin_params &fp) {
@@ -195,6 +200,10 @@ hipError_t sweep_update(lgf_ctx *c, int cur, void *D, T half_alpha, const fin_pa
         if (c->g.nc == 3)
             return launch_update<T>(c->g, c->L32[0], nullptr, D, P::field(c, cur ^ 1),
                                     acc_G(c, cur), half_alpha, c->exact_exp, acc_G(c, cur ^ 1),
+                                    c->partials, c->status, fp, c->stream);
+    } else {
+        if (c->g.keeps_u0())
+            return launch_update_u0(c->g, c->L64[0], acc_G64(c, cur ^ 1), P::field(c, cur ^ 1),
                                     c->partials, c->status, fp, c->stream);
     }
     return launch_update<T>(c->g, P::links(c, cur), P::links(c, cur ^ 1), D, P::field(c, cur ^ 1),
@@ -226,38 +235,58 @@ hipError_t transform_pass(lgf_ctx *c, bool f32, int pass, void *D) {
     return launch_fft_xy<double>(c->g, D, +1, c->tw64, c->plan64, c->status, c->stream);
 }
 
-// Pass `pass` (0..2) of sweep `cur`'s transform of field D (none without the
-// acceleration).  In the FP32 sweeps of an SU(3) mixed solve pass 2 also
-// accumulates G <- g G: fused into the inverse (x,y) pass when one block can
-// hold a plane of all four fields (xy_acc_fusable), else as a kernel after it.
+// Inverse (x,y) pass of a sweep that keeps U0 and G, with G <- g G: fused when
+// one block can hold a plane of all four fields (xy_acc_fusable), else as a
+// kernel after it (alone without the acceleration).  TF: real type of the
+// field, TG: of G.
+template <class TF, class TG>
+hipError_t acc_pass(lgf_ctx *c, void *D, const void *Gold, void *Gnew) {
+    constexpr bool f32 = std::is_same<TF, float>::value;
+    const fft_plan &pl = f32 ? c->plan32 : c->plan64;
+    const void *tw = f32 ? (const void *)c->tw32 : (const void *)c->tw64;
+    if (c->accelerate && xy_acc_fusable<TF, TG>(c->g, pl))
+        return launch_fft_xy_inv_acc<TF, TG>(c->g, D, tw, pl, Gold, Gnew, c->half_alpha,
+                                             c->exact_exp, c->status, c->stream);
+    if (c->accelerate) {
+        const hipError_t e = transform_pass(c, f32, 2, D);
+        if (e != hipSuccess) return e;
+    }
+    return launch_gauge_acc<TF, TG>(c->g, D, Gold, Gnew, c->half_alpha, c->exact_exp, c->status,
+                                    c->stream);
+}
+
+// Pass `pass` (0..2) of sweep `n` (of its phase)'s transform of field D (none
+// without the acceleration).  In sweeps that keep U0 and G (the FP32 sweeps of
+// an SU(3) mixed solve, FP64 sweeps with geom::keeps_u0) pass 2 also
+// accumulates G <- g G, from G = 1 in the first sweep.
 template <class T>
-hipError_t sweep_pass(lgf_ctx *c, int cur, void *D, T half_alpha, int pass) {
-    if constexpr (std::is_same<T, float>::value) {
-        if (c->g.nc == 3 && pass == 2) {
-            if (c->accelerate && xy_acc_fusable<float>(c->g, c->plan32))
-                return launch_fft_xy_inv_acc<float>(c->g, D, c->tw32, c->plan32, acc_G(c, cur),
-                                                    acc_G(c, cur ^ 1), c->half_alpha, c->exact_exp,
-                                                    c->status, c->stream);
-            if (c->accelerate) {
-                const hipError_t e = transform_pass(c, true, 2, D);
-                if (e != hipSuccess) return e;
-            }
-            return launch_gauge_acc(c->g, D, acc_G(c, cur), acc_G(c, cur ^ 1), c->half_alpha,
-                                    c->exact_exp, c->status, c->stream);
+hipError_t sweep_pass(lgf_ctx *c, int n, void *D, int pass) {
+    const int cur = n & 1;
+    if (pass == 2) {
+        if constexpr (std::is_same<T, float>::value) {
+            if (c->g.nc == 3)
+                return acc_pass<float, float>(c, D, n ? acc_G(c, cur) : nullptr, acc_G(c, cur ^ 1));
+        } else if (c->g.keeps_u0()) {
+            const double2 *Gold = n ? acc_G64(c, cur) : nullptr;
+            if (c->g.ff32)
+                return acc_pass<float, double>(c, D, Gold, acc_G64(c, cur ^ 1));
+            return acc_pass<double, double>(c, D, Gold, acc_G64(c, cur ^ 1));
         }
     }
     if (!c->accelerate) return hipSuccess;
     return transform_pass(c, field32<T>(c), pass, D);
 }
 
-// One Fourier-accelerated sweep from links/field buffer `cur` into `cur^1`.
+// Sweep n (counted from the phase's first, 0) from links/field buffer n & 1
+// into the other one.
 template <class T>
-hipError_t enqueue_sweep(lgf_ctx *c, int cur, T half_alpha, const fin_params &fp) {
+hipError_t enqueue_sweep(lgf_ctx *c, int n, T half_alpha, const fin_params &fp) {
     using P = prec<T>;
     hipError_t e;
+    const int cur = n & 1;
     void *D = P::field(c, cur);
     for (int pass = 0; pass < 3; ++pass)
-        if ((e = sweep_pass<T>(c, cur, D, half_alpha, pass)) != hipSuccess) return e;
+        if ((e = sweep_pass<T>(c, n, D, pass)) != hipSuccess) return e;
     return sweep_update<T>(c, cur, D, half_alpha, fp);
 }
 
@@ -320,8 +349,7 @@ int run_phase(lgf_ctx *c, double alpha, double tol, int max_iter, int hist_base,
     };
     auto enqueue_batch = [&](int k, int slot) -> int {
         for (int i = 0; i < k; ++i) {
-            const int cur = (enq + i) & 1;
-            HIPCHK(c, enqueue_sweep<T>(c, cur, half_alpha, fp));
+            HIPCHK(c, enqueue_sweep<T>(c, enq + i, half_alpha, fp));
         }
         enq += k;
         HIPCHK(c, hipMemcpyAsync(c->status_host + 1 + slot, c->status, sizeof(dev_status),
@@ -451,7 +479,7 @@ int profile_impl(lgf_ctx *c, const double *U, double alpha, int n, double *ms) {
     using P = prec<T>;
     const bool accG = std::is_same<T, float>::value;
     HIPCHK(c, launch_pack_links<T>(U, P::links(c, 0), c->g, c->stream));
-    if (accG) HIPCHK(c, launch_g_identity(c->G32, c->g, c->stream));
+    if (accG && c->g.nc == 2) HIPCHK(c, launch_g_identity(c->G32, c->g, c->stream));
     HIPCHK(c, launch_status_reset(c->status, 0, c->stream));
     HIPCHK(c, launch_div_reduce<T>(c->g, P::links(c, 0), P::field(c, 0), c->partials, c->status,
                                    finp(c, true, 0.0, n + 1, 0), c->stream));
@@ -467,11 +495,11 @@ int profile_impl(lgf_ctx *c, const double *U, double alpha, int n, double *ms) {
         hipError_t err = hipSuccess;
         auto chk = [&](hipError_t x) { if (err == hipSuccess) err = x; };
         chk(hipEventRecord(e[0], c->stream));
-        chk(sweep_pass<T>(c, cur, D, half_alpha, 0));
+        chk(sweep_pass<T>(c, it, D, 0));
         chk(hipEventRecord(e[1], c->stream));
-        chk(sweep_pass<T>(c, cur, D, half_alpha, 1));
+        chk(sweep_pass<T>(c, it, D, 1));
         chk(hipEventRecord(e[2], c->stream));
-        chk(sweep_pass<T>(c, cur, D, half_alpha, 2));
+        chk(sweep_pass<T>(c, it, D, 2));
         chk(hipEventRecord(e[3], c->stream));
         chk(sweep_update<T>(c, cur, D, half_alpha, finp(c, false)));
         chk(hipEventRecord(e[4], c->stream));
@@ -705,17 +733,25 @@ int lgf_set_theta_switch(lgf_ctx *c, double theta_switch) {
     return LGF_OK;
 }
 
+// The working links after n64 sweeps of the FP64 phase into the caller's array.
+static int write_back(lgf_ctx *c, int n64, double *U) {
+    if (c->g.keeps_u0() && n64 > 0)
+        HIPCHK(c, launch_unpack_rotated(c->L64[0], acc_G64(c, n64), U, c->g, c->stream));
+    else
+        HIPCHK(c, launch_unpack_links(c->L64[c->g.keeps_u0() ? 0 : n64 & 1], U, c->g, c->stream));
+    return LGF_OK;
+}
+
 static int solve(lgf_ctx *c, double *U, double alpha, double tol, int max_iter, lgf_result *res) {
     Timer tm;
     int rc = check_ctx(c);
     if (rc) return rc;
     dev_status st{};
     int n32 = 0, n64 = 0, code = ST_CONVERGED;
-    int cur64 = 0;
     if (c->precision == LGF_MIXED) {
         // FP32 phase on a downcast copy; G accumulates the applied transformation
         HIPCHK(c, launch_pack_links<float>(U, c->L32[0], c->g, c->stream));
-        HIPCHK(c, launch_g_identity(c->G32, c->g, c->stream));
+        if (c->g.nc == 2) HIPCHK(c, launch_g_identity(c->G32, c->g, c->stream));
         const double tol32 = std::max(tol, c->theta_switch);
         // the FP32 phase also ends when theta stops reaching new minima (its
         // rounding floor lies above the hand-over threshold)
@@ -723,6 +759,9 @@ static int solve(lgf_ctx *c, double *U, double alpha, double tol, int max_iter, 
         if (rc) return rc;
         n32 = st.n;
         code = st.code;
+        // SU(3): the first sweep starts from G = 1 without reading it
+        if (n32 == 0 && c->g.nc == 3)
+            HIPCHK(c, launch_g_identity(c->G32, c->g, c->stream));
         // hand-over: U = G U0 G^dagger in FP64 (G reunitarised in FP64); for
         // SU(3) fused with the FP64 phase's first divergence
         const bool refine = code == ST_CONVERGED || code == ST_MAXITER || code == ST_STALLED;
@@ -740,7 +779,6 @@ static int solve(lgf_ctx *c, double *U, double alpha, double tol, int max_iter, 
             if (rc) return rc;
             n64 = st.n;
             code = st.code;
-            cur64 = n64 & 1;
         }
     } else {
         HIPCHK(c, launch_pack_links<double>(U, c->L64[0], c->g, c->stream));
@@ -748,9 +786,9 @@ static int solve(lgf_ctx *c, double *U, double alpha, double tol, int max_iter, 
         if (rc) return rc;
         n64 = st.n;
         code = st.code;
-        cur64 = n64 & 1;
     }
-    HIPCHK(c, launch_unpack_links(c->L64[cur64], U, c->g, c->stream));
+    rc = write_back(c, n64, U);
+    if (rc) return rc;
     HIPCHK(c, hipStreamSynchronize(c->stream));
     c->hist_len = n32 + n64 + 1;
     const int out = status_to_code(code);
@@ -787,22 +825,24 @@ int lgf_iterate(lgf_ctx *c, double *U, double alpha, int n_iter, lgf_result *res
     int rc = check_ctx(c);
     if (rc) return rc;
     dev_status st{};
-    int n32 = 0, n64 = 0, cur64 = 0;
+    int n32 = 0, n64 = 0;
     if (c->precision == LGF_MIXED) {
         HIPCHK(c, launch_pack_links<float>(U, c->L32[0], c->g, c->stream));
-        HIPCHK(c, launch_g_identity(c->G32, c->g, c->stream));
+        if (c->g.nc == 2) HIPCHK(c, launch_g_identity(c->G32, c->g, c->stream));
         rc = run_phase<float>(c, alpha, 0.0, n_iter, 0, st);
         if (rc) return rc;
         n32 = st.n;
+        if (n32 == 0 && c->g.nc == 3)
+            HIPCHK(c, launch_g_identity(c->G32, c->g, c->stream));
         HIPCHK(c, launch_switch(c->g, acc_G(c, n32), U, c->L64[0], c->stream));
     } else {
         HIPCHK(c, launch_pack_links<double>(U, c->L64[0], c->g, c->stream));
         rc = run_phase<double>(c, alpha, 0.0, n_iter, 0, st);
         if (rc) return rc;
         n64 = st.n;
-        cur64 = n64 & 1;
     }
-    HIPCHK(c, launch_unpack_links(c->L64[cur64], U, c->g, c->stream));
+    rc = write_back(c, n64, U);
+    if (rc) return rc;
     double F = st.F, th = st.theta;
     if (c->precision == LGF_MIXED) {
         rc = eval_links64(c, U, F, th);

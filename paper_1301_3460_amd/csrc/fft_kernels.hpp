@@ -198,7 +198,7 @@ __global__ void __launch_bounds__(XY_BLOCK)
     for (int i = threadIdx.x; i < Lxy; i += XY_BLOCK) {
         const int y = i / Lx, x = i - y * Lx;
         const vec2_t<T> *q = lds + y * P + x;
-        accumulate_G<EXACT>(ld<T>(q), ld<T>(q + REG), ld<T>(q + 2 * REG), ld<T>(q + 3 * REG), c,
+        accumulate_G<EXACT, T, T>(ld<T>(q), ld<T>(q + REG), ld<T>(q + 2 * REG), ld<T>(q + 3 * REG), c,
                             Gold, Gnew, g.S, s0 + i);
     }
 }
@@ -415,7 +415,7 @@ __global__ void __launch_bounds__(tile2_acc_threads<RMAX>())
     for (int i = threadIdx.x; i < nel; i += tile2_acc_threads<RMAX>()) {
         const int ja = i % Na, jb = i / Na;
         const vec2_t<T> *q = lds + ja * PA + jb * PB;
-        accumulate_G<EXACT>(ld<T>(q), ld<T>(q + REG), ld<T>(q + 2 * REG), ld<T>(q + 3 * REG), c,
+        accumulate_G<EXACT, T, T>(ld<T>(q), ld<T>(q + REG), ld<T>(q + 2 * REG), ld<T>(q + 3 * REG), c,
                             Gold, Gnew, g.S, off + (unsigned)ja + (unsigned)jb * sb);
     }
 }
@@ -527,16 +527,16 @@ __global__ void __launch_bounds__(rc_max_threads<T>())
     for (int y = 0; y < NY; ++y) st<T>(p + (long)y * Lx, a[y]);
 }
 
-// Inverse (x, y) pass of the FP32 sweeps of an SU(3) mixed solve, fused with
+// Inverse (x, y) pass of the sweeps that keep U0 and G, fused with
 // the accumulation G(x) <- g(x) G(x): the block holds all 4 fields of its
 // plane, so after the inverse transform each site's 4 entries of L Delta are
 // gathered through LDS, g is formed (first-order or exact step, coefficient
 // c) and G is updated from Gold into Gnew.  L Delta itself is not stored (the
 // update reads only G).
-template <class T, int NY, bool EXACT>
+template <class T, class TG, int NY, bool EXACT>
 __global__ void __launch_bounds__(rc_max_threads<T>())
     k_fft_xy_rc_acc(geom g, const vec2_t<T> *__restrict__ D, const vec2_t<T> *__restrict__ tw,
-                    const vec2_t<T> *__restrict__ Gold, vec2_t<T> *__restrict__ Gnew, double c,
+                    const vec2_t<TG> *__restrict__ Gold, vec2_t<TG> *__restrict__ Gnew, double c,
                     const dev_status *__restrict__ status) {
     if (status->done) return;
     extern __shared__ unsigned char smem_raw[];
@@ -562,7 +562,7 @@ __global__ void __launch_bounds__(rc_max_threads<T>())
     for (int i = threadIdx.x; i < (int)Lxy; i += blockDim.x) {
         const int y = i / Lx, xx = i - y * Lx;
         const vec2_t<T> *q = lds + y * PJ + xx;
-        accumulate_G<EXACT>(ld<T>(q), ld<T>(q + SW), ld<T>(q + 2 * SW), ld<T>(q + 3 * SW), c, Gold,
+        accumulate_G<EXACT, T, TG>(ld<T>(q), ld<T>(q + SW), ld<T>(q + 2 * SW), ld<T>(q + 3 * SW), c, Gold,
                             Gnew, g.S, s0 + i);
     }
 }
@@ -975,7 +975,7 @@ template <class T> void fft_set_max_lds(const geom &g, const fft_plan &p) {
         set(reinterpret_cast<const void *>(&k_fft_axis<T, 0, 32>), ax);
     }
     if constexpr (std::is_same<T, float>::value) {
-        if (p.xy == 1 && xy_acc_fusable<T>(g, p)) {
+        if (p.xy == 1 && xy_acc_fusable<T, T>(g, p)) {
             const size_t b = (size_t)4 * g.Ly * (g.Lx + 1) * sizeof(vec2_t<T>);
             set(reinterpret_cast<const void *>(&k_fft_xy_acc<T, 16, true>), b);
             set(reinterpret_cast<const void *>(&k_fft_xy_acc<T, 16, false>), b);
@@ -1099,24 +1099,25 @@ hipError_t launch_fft_xy(const geom &g, void *D, int dir, const void *tw, const 
 template <class T> inline size_t xy_acc_lds_bytes(const geom &g) {
     return (size_t)4 * g.Ly * (g.Lx + 1) * sizeof(vec2_t<T>);
 }
-template <class T> bool xy_acc_fusable(const geom &g, const fft_plan &pl) {
+template <class T, class TG> bool xy_acc_fusable(const geom &g, const fft_plan &pl) {
     if (g.nc != 3 || g.nf != 4) return false;
-    if (pl.t2) return std::is_same<T, float>::value && 4 * pl.t2a.lds <= XY_ACC_LDS_MAX;
+    constexpr bool F32 = std::is_same<T, float>::value && std::is_same<TG, float>::value;
+    if (pl.t2) return F32 && 4 * pl.t2a.lds <= XY_ACC_LDS_MAX;
     if (pl.xy == 0) return xy_fields_per_block<T>(g) == 4;
-    if (pl.xy == 1) return xy_acc_lds_bytes<T>(g) <= XY_ACC_LDS_MAX;
+    if (pl.xy == 1) return F32 && xy_acc_lds_bytes<T>(g) <= XY_ACC_LDS_MAX;
     return false;
 }
 
-template <class T>
+template <class T, class TG>
 hipError_t launch_fft_xy_inv_acc(const geom &g, void *D, const void *tw, const fft_plan &pl,
                                  const void *Gold, void *Gnew, double c, bool exact,
                                  const dev_status *status, hipStream_t st) {
-    if (!xy_acc_fusable<T>(g, pl)) return hipErrorInvalidValue;
+    if (!xy_acc_fusable<T, TG>(g, pl)) return hipErrorInvalidValue;
     auto Dp = static_cast<const vec2_t<T> *>(D);
     auto twp = static_cast<const vec2_t<T> *>(tw);
-    auto Go = static_cast<const vec2_t<T> *>(Gold);
-    auto Gn = static_cast<vec2_t<T> *>(Gnew);
-    if constexpr (std::is_same<T, float>::value) {
+    auto Go = static_cast<const vec2_t<TG> *>(Gold);
+    auto Gn = static_cast<vec2_t<TG> *>(Gnew);
+    if constexpr (std::is_same<T, float>::value && std::is_same<TG, float>::value) {
         if (pl.t2) {
             const dim3 grid((unsigned)pl.t2a.nouter);
             const size_t b = 4 * pl.t2a.lds;
@@ -1133,21 +1134,21 @@ hipError_t launch_fft_xy_inv_acc(const geom &g, void *D, const void *tw, const f
 #undef LGF_TA
             return hipGetLastError();
         }
-    }
-    if (pl.xy == 1) {
-        const size_t b = xy_acc_lds_bytes<T>(g);
-        const dim3 grid((unsigned)(g.Lz * g.Lt));
-        const bool sm = fft_tier(g.Lx) <= 16 && fft_tier(g.Ly) <= 16;
+        if (pl.xy == 1) {
+            const size_t b = xy_acc_lds_bytes<T>(g);
+            const dim3 grid((unsigned)(g.Lz * g.Lt));
+            const bool sm = fft_tier(g.Lx) <= 16 && fft_tier(g.Ly) <= 16;
 #define LGF_XG(R, E) k_fft_xy_acc<T, R, E><<<grid, XY_BLOCK, b, st>>>(g, Dp, twp, Go, Gn, c, status)
-        if (sm) {
-            if (exact) LGF_XG(16, true);
-            else LGF_XG(16, false);
-        } else {
-            if (exact) LGF_XG(32, true);
-            else LGF_XG(32, false);
-        }
+            if (sm) {
+                if (exact) LGF_XG(16, true);
+                else LGF_XG(16, false);
+            } else {
+                if (exact) LGF_XG(32, true);
+                else LGF_XG(32, false);
+            }
 #undef LGF_XG
-        return hipGetLastError();
+            return hipGetLastError();
+        }
     }
     const size_t lds = pl.lds_xy;
     const dim3 grid((unsigned)(g.Lz * g.Lt));
@@ -1155,9 +1156,9 @@ hipError_t launch_fft_xy_inv_acc(const geom &g, void *D, const void *tw, const f
 #define LGF_XA(NN)                                                                            \
     case NN:                                                                                  \
         if (exact)                                                                            \
-            k_fft_xy_rc_acc<T, NN, true><<<grid, nt, lds, st>>>(g, Dp, twp, Go, Gn, c, status);  \
+            k_fft_xy_rc_acc<T, TG, NN, true><<<grid, nt, lds, st>>>(g, Dp, twp, Go, Gn, c, status);  \
         else                                                                                  \
-            k_fft_xy_rc_acc<T, NN, false><<<grid, nt, lds, st>>>(g, Dp, twp, Go, Gn, c, status); \
+            k_fft_xy_rc_acc<T, TG, NN, false><<<grid, nt, lds, st>>>(g, Dp, twp, Go, Gn, c, status); \
         break;
     switch (g.Ly) {
         LGF_FFT_SMALL_EXTENTS(LGF_XA)

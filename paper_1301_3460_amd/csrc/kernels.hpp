@@ -63,6 +63,9 @@ struct geom {
     int nc = 3, nf = 4;
     // 1: FP64 sweeps keep the Fourier field (Delta, L Delta) in FP32
     int ff32 = 0;
+    // FP64 sweeps keep the input links U0 and the accumulated transformation
+    // G instead of storing the links of every sweep (keeps_u0)
+    bool keeps_u0() const;
 };
 
 constexpr int SITE_BLOCK = 256;  // threads per block of the site kernels
@@ -93,6 +96,16 @@ inline geom make_geom(const int L[4], int nc) {
     return g;
 }
 
+// FP64 sweeps of 12-real SU(3) links keep U0 and G from this volume on.  Such
+// a sweep moves 1056 bytes per site (update 544, inverse pass with G 256, the
+// other two passes 128 each) where one that stores its links moves 1280, but
+// its inverse pass also reads and writes G: per sweep, stored links against
+// U0 and G, 48.0 / 49.3 us at 18^2 x 12 x 9 (34992 sites), 53.0 / 50.0 at 16^4,
+// 74.8 / 66.6 at 16^3 x 32, 135 / 109 at 24^4, 290 / 284 at 32^4 and
+// 1783 / 1752 at 48^4, whose inverse (x,t) pass leaves G to a kernel of its own.
+constexpr long KEEP_U0_MIN_SITES = 49152;
+inline bool geom::keeps_u0() const { return nc == 3 && lf == 12 && V >= KEEP_U0_MIN_SITES; }
+
 // All launchers enqueue on `st` and return hipGetLastError().
 template <class T>
 hipError_t launch_pack_links(const double *Uaos, void *L, const geom &g, hipStream_t st);
@@ -115,6 +128,16 @@ template <class T>
 hipError_t launch_update(const geom &g, const void *Lin, void *Lout, const void *LD, void *Dout,
                          void *G, T c, bool exact, void *GX, double *partials, dev_status *status,
                          const fin_params &fp, hipStream_t st);
+
+// The update of FP64 sweeps that keep U0 and G (geom::keeps_u0): the next
+// Delta and the partials of F and theta of the links G U0 G^dagger, which are
+// not stored.
+hipError_t launch_update_u0(const geom &g, const void *U0, const void *G, void *Dout,
+                            double *partials, dev_status *status, const fin_params &fp,
+                            hipStream_t st);
+// Caller links U_mu(x) = G(x) U0_mu(x) G(x+mu)^dagger from U0 (SoA, 12 reals)
+hipError_t launch_unpack_rotated(const void *U0, const void *G, double *Uaos, const geom &g,
+                                 hipStream_t st);
 
 // One-axis pass of the 4D transform: a block holds W consecutive elements of
 // the axis's inner range (the sites below the axis: none for x, x for y, the
@@ -186,17 +209,19 @@ void update_set_max_lds();
 template <class T>
 hipError_t launch_fft_xy(const geom &g, void *D, int dir, const void *tw, const fft_plan &pl,
                          const dev_status *status, hipStream_t st);
-// Inverse (x,y) pass fused with G(x) <- g(x) G(x) (FP32 sweeps of an SU(3)
-// mixed solve; L Delta itself is not stored), when xy_acc_fusable: register-
-// column planes with all 4 fields in one block, or wider planes whose 4
-// fields fit in LDS together.
-template <class T> bool xy_acc_fusable(const geom &g, const fft_plan &pl);
-template <class T>
+// Inverse (x,y) pass on the field of real type T fused with G(x) <- g(x) G(x),
+// G of real type TG (SU(3) sweeps that keep U0 and G; L Delta itself is not
+// stored), when xy_acc_fusable: register-column planes with all 4 fields in
+// one block or, in FP32 sweeps, wider planes whose 4 fields fit in LDS
+// together.  Gold == nullptr: the first sweep, G = 1.
+template <class T, class TG> bool xy_acc_fusable(const geom &g, const fft_plan &pl);
+template <class T, class TG>
 hipError_t launch_fft_xy_inv_acc(const geom &g, void *D, const void *tw, const fft_plan &pl,
                                  const void *Gold, void *Gnew, double c, bool exact,
                                  const dev_status *status, hipStream_t st);
-// G(x) <- g(x) G(x) from the field L Delta as a kernel of its own (FP32 sweeps
-// of an SU(3) mixed solve whose inverse (x,y) pass cannot take it)
+// G(x) <- g(x) G(x) from the field L Delta (real type TF) as a kernel of its
+// own (sweeps whose inverse (x,y) pass cannot take it)
+template <class TF, class TG>
 hipError_t launch_gauge_acc(const geom &g, const void *LD, const void *Gold, void *Gnew, double c,
                             bool exact, const dev_status *status, hipStream_t st);
 // (z,t) transform.  mode 0: forward, scale by p2max/(V p2), inverse; -1:

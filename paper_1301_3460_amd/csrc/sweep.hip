@@ -353,6 +353,168 @@ __global__ void __launch_bounds__(SITE_BLOCK)
 }
 
 // ---------------------------------------------------------------------------
+// FP64 sweeps that keep the input links U0 and the transformation G
+// ---------------------------------------------------------------------------
+
+// The next Delta and the partials of F and theta of the links
+// U_mu(x) = G(x) U0_mu(x) G(x+mu)^dagger, which are formed and not stored: 544
+// bytes per site (R U0 384, R G 96, W Delta 64) instead of the 896 of k_update
+// (R links, W links, R L Delta, W Delta).  With
+//   K(x) = sum_mu [U0_mu(x) G(x+mu)^dagger + (G(x-mu) U0_mu(x-mu))^dagger]
+// the sum over mu of U_mu(x) + U_mu(x-mu)^dagger is M = G(x) K(x), so that
+// X - X^dagger = M^dagger - M and the eight links need nine matrix products
+// instead of sixteen; sum_mu Re Tr U_mu over the lattice is half that of M.
+// Each product is a matrix of SU(3): rows 0,1 by products, row 2 completed.
+// At 32^4 146 us against 195 for k_update (event timing; 725 MB of measured
+// traffic against 1060).  Its time is that of its reads: a kernel that only
+// streams U0 and G and writes Delta takes 122 us, and one whose eight
+// neighbours are its own site 142.  206 VGPRs, two waves per SIMD: with three
+// (168 VGPRs) 152 us, with four and no load ahead 169, as more blocks in
+// flight find fewer neighbour lines in L2.  Marking the loads of U0 as
+// streaming costs the L2 reuse of U0(x-mu): 171 us.
+template <class TF>
+__global__ void __launch_bounds__(SITE_BLOCK)
+    k_update_u0(geom g, const double2 *__restrict__ U0, const double2 *__restrict__ G,
+                vec2_t<TF> *__restrict__ Dout, double *__restrict__ partials,
+                const dev_status *__restrict__ status) {
+    using T = double;
+    if (status->done) return;
+    const long s = block_site(g, blockIdx.x, gridDim.x, threadIdx.x);
+    double fs = 0, ts = 0;
+    if (s < g.V) {
+        const nbr n = neighbours(g, s);
+        struct half {
+            cpx<T> f[6], u[6];
+        };
+        // half-steps h = 2 mu + b as in k_update: b = 0 the link leaving x, b = 1
+        // the one arriving from x - mu; one ahead in flight
+        auto fetch = [&](int h, half &d) {
+            const int mu = h >> 1;
+            const long sf = (h & 1) ? n.m[mu] : n.p[mu];
+            const long sl = (h & 1) ? n.m[mu] : s;
+#pragma unroll
+            for (int k = 0; k < 6; ++k) d.f[k] = ld<T>(G + (long)k * g.S + sf);
+            const double2 *lp = U0 + (long)mu * 6 * g.S + sl;
+#pragma unroll
+            for (int k = 0; k < 6; ++k) d.u[k] = ld<T>(lp + (long)k * g.S);
+        };
+        auto rows01 = [](const cpx<T> (&f)[6]) {
+            mat3<T> m;
+#pragma unroll
+            for (int k = 0; k < 6; ++k) m.e[k / 3][k % 3] = f[k];
+            return m;
+        };
+        half d[2];
+        fetch(0, d[0]);
+        mat3<T> K;
+#pragma unroll
+        for (int k = 0; k < 9; ++k) K.e[k / 3][k % 3] = mk<T>(0, 0);
+#pragma unroll
+        for (int h = 0; h < 8; ++h) {
+            if (h < 7) fetch(h + 1, d[(h + 1) & 1]);
+            __builtin_amdgcn_sched_barrier(0);
+            const half &cur = d[h & 1];
+            mat3<T> gn = rows01(cur.f), u = rows01(cur.u), p;
+            if ((h & 1) == 0) {
+                rebuild_row2(gn);  // rows 0,1 of U0 G^dagger need rows 0,1 of U0
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int j = 0; j < 3; ++j) {
+                        cpx<T> a = cmulc(u.e[i][0], gn.e[j][0]);
+                        a = cmacc(a, u.e[i][1], gn.e[j][1]);
+                        p.e[i][j] = cmacc(a, u.e[i][2], gn.e[j][2]);
+                    }
+                rebuild_row2(p);
+#pragma unroll
+                for (int k = 0; k < 9; ++k)
+                    K.e[k / 3][k % 3] = K.e[k / 3][k % 3] + p.e[k / 3][k % 3];
+            } else {
+                rebuild_row2(u);  // rows 0,1 of G U0 need rows 0,1 of G
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int j = 0; j < 3; ++j) {
+                        cpx<T> a = cmul(gn.e[i][0], u.e[0][j]);
+                        a = cmac(a, gn.e[i][1], u.e[1][j]);
+                        p.e[i][j] = cmac(a, gn.e[i][2], u.e[2][j]);
+                    }
+                rebuild_row2(p);
+#pragma unroll
+                for (int k = 0; k < 9; ++k)
+                    K.e[k / 3][k % 3] = K.e[k / 3][k % 3] + conjg(p.e[k % 3][k / 3]);
+            }
+        }
+        mat3<T> g0;
+#pragma unroll
+        for (int k = 0; k < 6; ++k) g0.e[k / 3][k % 3] = ld<T>(G + (long)k * g.S + s);
+        rebuild_row2(g0);
+        xacc<T> X;
+        xacc_zero(X);
+        mat3<T> M;
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                cpx<T> a = cmul(g0.e[i][0], K.e[0][j]);
+                a = cmac(a, g0.e[i][1], K.e[1][j]);
+                M.e[i][j] = cmac(a, g0.e[i][2], K.e[2][j]);
+            }
+        xacc_add(X, M, T(-1));
+        cpx<T> f0, f1, f2, f3;
+        ts = delta_pack(X, f0, f1, f2, f3);
+        fs = 0.5 * retrace(M);
+        st_stream<TF>(Dout + s, cvt<TF>(f0));
+        st_stream<TF>(Dout + g.S + s, cvt<TF>(f1));
+        st_stream<TF>(Dout + 2 * g.S + s, cvt<TF>(f2));
+        st_stream<TF>(Dout + 3 * g.S + s, cvt<TF>(f3));
+    }
+    block_sum2<SITE_BLOCK>(fs, ts, partials, blockIdx.x);
+}
+
+// The caller's links G(x) U0_mu(x) G(x+mu)^dagger at the end of such a phase.
+// A wave's 64 sites are consecutive (block_site), so each wave stages its 64
+// links of one direction in LDS and writes them as one contiguous run.
+__global__ void __launch_bounds__(SITE_BLOCK)
+    k_unpack_rotated(geom g, const double2 *__restrict__ U0, const double2 *__restrict__ G,
+                     double2 *__restrict__ U) {
+    __shared__ double2 buf[SITE_BLOCK * 9];
+    const long s = block_site(g, blockIdx.x, gridDim.x, threadIdx.x);
+    const int lane = threadIdx.x & 63;
+    double2 *mine = buf + (threadIdx.x - lane) * 9;
+    const long s0 = s - lane;  // first site of the wave
+    const int cnt = (int)(g.V - s0 < 64 ? (g.V > s0 ? g.V - s0 : 0) : 64) * 9;
+    const bool live = s < g.V;
+    nbr n{};
+    mat3<double> g0;
+    auto load_G = [&](long q) {
+        mat3<double> m;
+#pragma unroll
+        for (int k = 0; k < 6; ++k) m.e[k / 3][k % 3] = ld<double>(G + (long)k * g.S + q);
+        rebuild_row2(m);
+        return m;
+    };
+    if (live) {
+        n = neighbours(g, s);
+        g0 = load_G(s);
+    }
+#pragma unroll
+    for (int mu = 0; mu < 4; ++mu) {
+        if (live) {
+            const mat3<double> r =
+                mul_abcd<2>(g0, load_link<double, 12>(U0, g.S, mu, s), load_G(n.p[mu]));
+#pragma unroll
+            for (int k = 0; k < 9; ++k)
+                mine[lane * 9 + k] = make_double2(r.e[k / 3][k % 3].re, r.e[k / 3][k % 3].im);
+        }
+        __syncthreads();
+        double2 *u = U + ((long)mu * g.V + s0) * 9;
+        for (int e = lane; e < cnt; e += 64) u[e] = mine[e];
+        __syncthreads();
+    }
+}
+
+// ---------------------------------------------------------------------------
 // FP32 sweeps of an SU(3) mixed solve with the links shared through LDS
 // ---------------------------------------------------------------------------
 
@@ -1054,19 +1216,19 @@ __global__ void __launch_bounds__(256)
     for (int k = 0; k < 6; ++k) st<T>(GX + (long)k * g.S + s, m.e[k / 3][k % 3]);
 }
 
-// FP32 sweeps of a mixed solve: G(x) <- g(x) G(x), rows 0,1 kept (12 reals),
+// Sweeps that keep U0 and G: G(x) <- g(x) G(x), rows 0,1 kept (12 reals),
 // from Gold into Gnew (the update then forms G(x) U0 G(x+mu)^dagger at x and
 // its neighbours from Gnew; the old G stays readable for those neighbours).
 // g and the product are formed and reunitarised in FP64 (accumulate_G).
-template <bool EXACT>
+template <bool EXACT, class TF, class TG>
 __global__ void __launch_bounds__(256)
-    k_gauge_acc(geom g, const float2 *__restrict__ LD, const float2 *__restrict__ Gold,
-                float2 *__restrict__ Gnew, double c, const dev_status *__restrict__ status) {
+    k_gauge_acc(geom g, const vec2_t<TF> *__restrict__ LD, const vec2_t<TG> *__restrict__ Gold,
+                vec2_t<TG> *__restrict__ Gnew, double c, const dev_status *__restrict__ status) {
     if (status->done) return;
     const long s = (long)blockIdx.x * blockDim.x + threadIdx.x;
     if (s >= g.V) return;
-    accumulate_G<EXACT>(ld<float>(LD + s), ld<float>(LD + g.S + s), ld<float>(LD + 2 * g.S + s),
-                        ld<float>(LD + 3 * g.S + s), c, Gold, Gnew, g.S, s);
+    accumulate_G<EXACT, TF, TG>(ld<TF>(LD + s), ld<TF>(LD + g.S + s), ld<TF>(LD + 2 * g.S + s),
+                                ld<TF>(LD + 3 * g.S + s), c, Gold, Gnew, g.S, s);
 }
 
 // The Fourier field is FP32 for FP32 sweeps and, when g.ff32 is set, for FP64
@@ -1161,14 +1323,51 @@ hipError_t launch_update(const geom &g, const void *Lin, void *Lout, const void 
     if (fp.enabled) k_finalize<<<1, FIN_BLOCK, 0, st>>>(partials, site_blocks(g.V), status, fp);
     return hipGetLastError();
 }
+template <class TF, class TG>
 hipError_t launch_gauge_acc(const geom &g, const void *LD, const void *Gold, void *Gnew, double c,
                             bool exact, const dev_status *status, hipStream_t st) {
     if (g.nc != 3) return hipErrorInvalidValue;
-    auto LDp = static_cast<const float2 *>(LD);
-    auto Go = static_cast<const float2 *>(Gold);
-    auto Gn = static_cast<float2 *>(Gnew);
-    if (exact) k_gauge_acc<true><<<nblk(g.V, 256), 256, 0, st>>>(g, LDp, Go, Gn, c, status);
-    else k_gauge_acc<false><<<nblk(g.V, 256), 256, 0, st>>>(g, LDp, Go, Gn, c, status);
+    auto LDp = static_cast<const vec2_t<TF> *>(LD);
+    auto Go = static_cast<const vec2_t<TG> *>(Gold);
+    auto Gn = static_cast<vec2_t<TG> *>(Gnew);
+    if (exact)
+        k_gauge_acc<true, TF, TG><<<nblk(g.V, 256), 256, 0, st>>>(g, LDp, Go, Gn, c, status);
+    else
+        k_gauge_acc<false, TF, TG><<<nblk(g.V, 256), 256, 0, st>>>(g, LDp, Go, Gn, c, status);
+    return hipGetLastError();
+}
+template hipError_t launch_gauge_acc<float, float>(const geom &, const void *, const void *, void *,
+                                                   double, bool, const dev_status *, hipStream_t);
+template hipError_t launch_gauge_acc<float, double>(const geom &, const void *, const void *,
+                                                    void *, double, bool, const dev_status *,
+                                                    hipStream_t);
+template hipError_t launch_gauge_acc<double, double>(const geom &, const void *, const void *,
+                                                     void *, double, bool, const dev_status *,
+                                                     hipStream_t);
+
+hipError_t launch_update_u0(const geom &g, const void *U0, const void *G, void *Dout,
+                            double *partials, dev_status *status, const fin_params &fp,
+                            hipStream_t st) {
+    if (!g.keeps_u0()) return hipErrorInvalidValue;
+    auto go = [&](auto kernel, auto *D) {
+        kernel<<<site_blocks(g.V), SITE_BLOCK, 0, st>>>(g, static_cast<const double2 *>(U0),
+                                                        static_cast<const double2 *>(G), D,
+                                                        partials, status);
+    };
+    if (g.ff32) go(k_update_u0<float>, static_cast<float2 *>(Dout));
+    else go(k_update_u0<double>, static_cast<double2 *>(Dout));
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    if (fp.enabled) k_finalize<<<1, FIN_BLOCK, 0, st>>>(partials, site_blocks(g.V), status, fp);
+    return hipGetLastError();
+}
+
+hipError_t launch_unpack_rotated(const void *U0, const void *G, double *Uaos, const geom &g,
+                                 hipStream_t st) {
+    if (!g.keeps_u0()) return hipErrorInvalidValue;
+    k_unpack_rotated<<<site_blocks(g.V), SITE_BLOCK, 0, st>>>(
+        g, static_cast<const double2 *>(U0), static_cast<const double2 *>(G),
+        reinterpret_cast<double2 *>(Uaos));
     return hipGetLastError();
 }
 
