@@ -70,9 +70,6 @@ struct lgf_ctx {
     double *reduce_host = nullptr;      // pinned [2]
     double *histF = nullptr, *histT = nullptr;
     int hist_len = 0;
-    // differentiation scratch (allocated on first use)
-    double *gaos = nullptr;   // V*9 complex or 4V*9 complex (link exponentials)
-    double2 *Lrot = nullptr;  // 12-real FP64 links (differentiation scratch)
     // exactly exponentiated g, rows 0,1 (SU(3) exact step; allocated when enabled)
     double2 *Gex = nullptr;
     std::string err;
@@ -435,35 +432,7 @@ int check_ctx(lgf_ctx *c) {
     return LGF_OK;
 }
 
-// Pack caller links into FP64 working buffer 0 (12-real form), then F/theta
-// of them.
-int eval_links64(lgf_ctx *c, const double *U, double &F, double &theta) {
-    const geom g = g12(c);
-    HIPCHK(c, launch_pack_links<double>(U, c->L64[0], g, c->stream));
-    HIPCHK(c, launch_status_reset(c->status, 0, c->stream));
-    HIPCHK(c, launch_div_reduce<double>(g, c->L64[0], c->D64[0], c->partials, c->status,
-                                        finp(c, false), c->stream));
-    HIPCHK(c, launch_reduce_only(c->partials, c->nparts, c->reduce_out, c->stream));
-    HIPCHK(c, hipMemcpyAsync(c->reduce_host, c->reduce_out, 2 * sizeof(double),
-                             hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(c, hipStreamSynchronize(c->stream));
-    F = c->reduce_host[0] * normF(c);
-    theta = c->reduce_host[1] * normT(c);
-    return LGF_OK;
-}
-
-int ensure_diff_scratch(lgf_ctx *c) {
-    if (!c->gaos) {
-        if (hipMalloc(&c->gaos, (size_t)4 * c->g.V * 9 * sizeof(double2)) != hipSuccess)
-            return fail(c, LGF_ERR_OOM, "out of device memory (differentiation scratch)");
-    }
-    if (!c->Lrot) {
-        if (hipMalloc(&c->Lrot, (size_t)24 * c->g.S * sizeof(double2)) != hipSuccess)
-            return fail(c, LGF_ERR_OOM, "out of device memory (differentiation scratch)");
-    }
-    return LGF_OK;
-}
-
+// Sums the partials of a measurement into reduce_host and waits for the stream.
 int sum_partials(lgf_ctx *c, double &A, double &B) {
     HIPCHK(c, launch_reduce_only(c->partials, c->nparts, c->reduce_out, c->stream));
     HIPCHK(c, hipMemcpyAsync(c->reduce_host, c->reduce_out, 2 * sizeof(double),
@@ -471,6 +440,25 @@ int sum_partials(lgf_ctx *c, double &A, double &B) {
     HIPCHK(c, hipStreamSynchronize(c->stream));
     A = c->reduce_host[0];
     B = c->reduce_host[1];
+    return LGF_OK;
+}
+
+// F and theta of the caller's links
+int eval_links64(lgf_ctx *c, const double *U, double &F, double &theta) {
+    if (c->g.nc == 3) {
+        HIPCHK(c, launch_div_aos(c->g, U, nullptr, 0, c->partials, c->stream));
+    } else {
+        const geom g = g12(c);
+        HIPCHK(c, launch_pack_links<double>(U, c->L64[0], g, c->stream));
+        HIPCHK(c, launch_status_reset(c->status, 0, c->stream));
+        HIPCHK(c, launch_div_reduce<double>(g, c->L64[0], c->D64[0], c->partials, c->status,
+                                            finp(c, false), c->stream));
+    }
+    double A, B;
+    const int rc = sum_partials(c, A, B);
+    if (rc) return rc;
+    F = A * normF(c);
+    theta = B * normT(c);
     return LGF_OK;
 }
 
@@ -674,7 +662,7 @@ void lgf_destroy(lgf_ctx *c) {
     else (void)hipDeviceSynchronize();
     void *dev[] = {c->L64[0], c->L64[1], c->D64[0], c->D64[1], c->G32, c->tw64, c->tw32,
                    c->pt64, c->pt32, c->partials, c->status, c->reduce_out, c->histF, c->histT,
-                   c->gaos, c->Lrot, c->Gex};
+                   c->Gex};
     for (void *p : dev)
         if (p) (void)hipFree(p);
     if (c->status_host) (void)hipHostFree(c->status_host);
@@ -868,12 +856,12 @@ int lgf_functional(lgf_ctx *c, const double *U, const double *g, double *F) {
     if (!U || !F) return fail(c, LGF_ERR_ARG, "null argument");
     int rc = check_ctx(c);
     if (rc) return rc;
-    if (!g) {
+    if (!g && c->g.nc == 2) {
         double th;
         return eval_links64(c, U, *F, th);
     }
-    HIPCHK(c, launch_pack_links<double>(U, c->L64[0], g12(c), c->stream));
-    HIPCHK(c, launch_functional_g(c->g, c->L64[0], g, c->partials, c->stream));
+    if (!g) HIPCHK(c, launch_trace_aos(c->g, U, c->partials, c->stream));
+    else HIPCHK(c, launch_functional_g(c->g, U, g, c->partials, c->stream));
     double A, B;
     rc = sum_partials(c, A, B);
     if (rc) return rc;
@@ -896,8 +884,7 @@ int lgf_plaquette(lgf_ctx *c, const double *U, double *P) {
     if (!U || !P) return fail(c, LGF_ERR_ARG, "null argument");
     int rc = check_ctx(c);
     if (rc) return rc;
-    HIPCHK(c, launch_pack_links<double>(U, c->L64[0], g12(c), c->stream));
-    HIPCHK(c, launch_plaquette(c->g, c->L64[0], c->partials, c->stream));
+    HIPCHK(c, launch_plaquette(c->g, U, c->partials, c->stream));
     double A, B;
     rc = sum_partials(c, A, B);
     if (rc) return rc;
@@ -911,11 +898,8 @@ int lgf_divergence(lgf_ctx *c, const double *U, double *Delta) {
     if (!U || !Delta) return fail(c, LGF_ERR_ARG, "null argument");
     int rc = check_ctx(c);
     if (rc) return rc;
-    HIPCHK(c, launch_pack_links<double>(U, c->L64[0], g12(c), c->stream));
-    HIPCHK(c, launch_status_reset(c->status, 0, c->stream));
-    HIPCHK(c, launch_div_reduce<double>(g12(c), c->L64[0], c->D64[0], c->partials, c->status,
-                                        finp(c, false), c->stream));
-    HIPCHK(c, launch_matrix_from_field(c->D64[0], Delta, c->g.V, c->g.S, c->stream));
+    HIPCHK(c, launch_div_aos(c->g, U, reinterpret_cast<double2 *>(Delta), 1, c->partials,
+                             c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     return LGF_OK;
 }
@@ -976,9 +960,12 @@ int lgf_functional_omega(lgf_ctx *c, const double *U, const double *omega, doubl
     if (!U || !omega || !F) return fail(c, LGF_ERR_ARG, "null argument");
     int rc = check_ctx(c);
     if (rc) return rc;
-    if ((rc = ensure_diff_scratch(c))) return rc;
-    HIPCHK(c, launch_expm_sites(omega, c->gaos, c->g.V, c->stream));
-    return lgf_functional(c, U, c->gaos, F);
+    HIPCHK(c, launch_functional_omega(c->g, U, omega, c->L64[0], c->partials, c->stream));
+    double A, B;
+    rc = sum_partials(c, A, B);
+    if (rc) return rc;
+    *F = A * normF(c);
+    return LGF_OK;
 }
 
 int lgf_functional_omega_grad(lgf_ctx *c, const double *U, const double *omega, double *F,
@@ -988,19 +975,11 @@ int lgf_functional_omega_grad(lgf_ctx *c, const double *U, const double *omega, 
     if (!U || !omega || !F || !dF) return fail(c, LGF_ERR_ARG, "null argument");
     int rc = check_ctx(c);
     if (rc) return rc;
-    if ((rc = ensure_diff_scratch(c))) return rc;
-    HIPCHK(c, launch_expm_sites(omega, c->gaos, c->g.V, c->stream));
-    HIPCHK(c, launch_pack_links<double>(U, c->L64[0], g12(c), c->stream));
-    HIPCHK(c, launch_rotate_links(c->g, c->L64[0], c->gaos, c->Lrot, c->stream));
-    HIPCHK(c, launch_status_reset(c->status, 0, c->stream));
-    HIPCHK(c, launch_div_reduce<double>(g12(c), c->Lrot, c->D64[0], c->partials, c->status,
-                                        finp(c, false), c->stream));
+    HIPCHK(c, launch_omega_grad(c->g, U, omega, c->L64[0], dF, normF(c), c->partials, c->stream));
     double A, B;
     rc = sum_partials(c, A, B);
     if (rc) return rc;
     *F = A * normF(c);
-    HIPCHK(c, launch_omega_grad(c->g, c->D64[0], omega, dF, normF(c), c->stream));
-    HIPCHK(c, hipStreamSynchronize(c->stream));
     return LGF_OK;
 }
 
@@ -1010,25 +989,15 @@ int lgf_theta_grad(lgf_ctx *c, const double *U, const double *eps, double *theta
     if (!U || !theta) return fail(c, LGF_ERR_ARG, "null argument");
     int rc = check_ctx(c);
     if (rc) return rc;
-    if ((rc = ensure_diff_scratch(c))) return rc;
-    HIPCHK(c, launch_pack_links<double>(U, c->L64[0], g12(c), c->stream));
-    const void *Lw = c->L64[0];
-    if (eps) {
-        HIPCHK(c, launch_expm_sites(eps, c->gaos, 4 * c->g.V, c->stream));
-        HIPCHK(c, launch_left_multiply_links(c->L64[0], c->gaos, c->Lrot, c->g.V, c->g.S, c->stream));
-        Lw = c->Lrot;
-    }
-    HIPCHK(c, launch_status_reset(c->status, 0, c->stream));
-    HIPCHK(c, launch_div_reduce<double>(g12(c), Lw, c->D64[0], c->partials, c->status,
-                                        finp(c, false), c->stream));
+    HIPCHK(c, launch_theta_links(c->g, U, eps, c->L64[0], dtheta ? c->D64[0] : nullptr, c->partials,
+                                 c->stream));
+    if (dtheta)
+        HIPCHK(c, launch_theta_grad(c->g, U, eps, c->L64[0], c->D64[0], dtheta, normT(c),
+                                    c->stream));
     double A, B;
     rc = sum_partials(c, A, B);
     if (rc) return rc;
     *theta = B * normT(c);
-    if (dtheta) {
-        HIPCHK(c, launch_theta_grad(c->g, Lw, c->D64[0], eps, dtheta, normT(c), c->stream));
-        HIPCHK(c, hipStreamSynchronize(c->stream));
-    }
     return LGF_OK;
 }
 
@@ -1068,9 +1037,11 @@ int lgf_measure_noalloc(const int L[4], const double *U, double *out, void *stre
     double *partials = nullptr;
     const int rc = noalloc_scratch(&partials);
     if (rc) return rc;
-    const hipError_t e =
-        launch_measure_aos(g, U, partials, out, 1.0 / (4.0 * 3.0 * (double)g.V),
-                           1.0 / (3.0 * (double)g.V), static_cast<hipStream_t>(stream));
+    const hipStream_t st = static_cast<hipStream_t>(stream);
+    hipError_t e = launch_div_aos(g, U, nullptr, 0, partials, st);
+    if (e == hipSuccess)
+        e = launch_measure_finalize(partials, site_blocks(g.V), out, 1.0 / (4.0 * 3.0 * (double)g.V),
+                                    1.0 / (3.0 * (double)g.V), st);
     if (e != hipSuccess)
         return fail(nullptr, LGF_ERR_DEVICE, std::string("launch failed: ") + hipGetErrorString(e));
     return LGF_OK;

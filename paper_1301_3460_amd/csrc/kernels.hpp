@@ -236,15 +236,6 @@ hipError_t launch_fft_zt(const geom &g, void *D, int mode, const void *tw, const
 hipError_t launch_reorder_fields(const geom &g, const double2 *in, long si, double2 *out, long so,
                                  int to_natural, hipStream_t st);
 
-// F = normF sum Re Tr U and theta = normT sum Tr[Delta Delta^+] of the
-// complex128 AoS links Uaos ([4][V][3][3], rows 0,1 read) into out[0..1]
-// (device), with the block partials in `partials` (site_blocks(V) pairs): the
-// arithmetic of launch_div_reduce + launch_reduce_only on packed links, in
-// the same order, without packing them (nothing is allocated or written
-// besides partials and out).
-hipError_t launch_measure_aos(const geom &g, const double *Uaos, double *partials, double *out,
-                              double normF, double normT, hipStream_t st);
-
 hipError_t launch_finalize(const double *partials, int nparts, dev_status *status,
                            const fin_params &fp, hipStream_t st);
 hipError_t launch_status_reset(dev_status *status, int hist_base, hipStream_t st);
@@ -262,20 +253,31 @@ hipError_t launch_switch_div(const geom &g, const void *G32, const double *U0aos
 hipError_t launch_field_from_matrix(const double *Maos, void *D64, long V, long S, hipStream_t st);
 hipError_t launch_matrix_from_field(const void *D64, double *Maos, long V, long S, hipStream_t st);
 
-hipError_t launch_plaquette(const geom &g, const void *L64, double *partials, hipStream_t st);
-hipError_t launch_functional_g(const geom &g, const void *L64, const double *gaos,
-                               double *partials, hipStream_t st);
-
-// differentiation (FP64)
-hipError_t launch_expm_sites(const double *omega, double *gaos, long n, hipStream_t st);
-hipError_t launch_rotate_links(const geom &g, const void *Lin, const double *gaos, void *Lout,
+// Measurements and differentiation (measure.hip, SU(3), FP64), from the
+// caller's links U (complex128 AoS [4][V][3][3], rows 0,1 read); the sums go
+// into `partials` (site_blocks(V) pairs, the first of each pair F's and the
+// second theta's).
+hipError_t launch_trace_aos(const geom &g, const double *U, double *partials, hipStream_t st);
+// out: Delta as four fields of stride S, as 3x3 matrices, or not wanted (null)
+hipError_t launch_div_aos(const geom &g, const double *U, double2 *out, int matrices,
+                          double *partials, hipStream_t st);
+hipError_t launch_plaquette(const geom &g, const double *U, double *partials, hipStream_t st);
+hipError_t launch_functional_g(const geom &g, const double *U, const double *gaos, double *partials,
                                hipStream_t st);
-hipError_t launch_left_multiply_links(const void *Lin, const double *eaos, void *Lout, long V,
-                                      long S, hipStream_t st);
-hipError_t launch_omega_grad(const geom &g, const void *D64, const double *omega, double *dF,
-                             double normF, hipStream_t st);
-hipError_t launch_theta_grad(const geom &g, const void *L64, const void *D64, const double *eps,
-                             double *dth, double normT, hipStream_t st);
+// F = normF A, theta = normT B of the partials' sums into out[0..1] (device)
+hipError_t launch_measure_finalize(const double *partials, int nparts, double *out, double normF,
+                                   double normT, hipStream_t st);
+// G (scratch, 6 components of stride S) = exp(i omega.T); F_U[G], and dF/domega
+hipError_t launch_functional_omega(const geom &g, const double *U, const double *omega, double2 *G,
+                                   double *partials, hipStream_t st);
+hipError_t launch_omega_grad(const geom &g, const double *U, const double *omega, double2 *G,
+                             double *dF, double normF, double *partials, hipStream_t st);
+// L (scratch, 12-real links) = exp(i eps.T) U, their sums and, if D is given,
+// their Delta (eps null: the links U themselves, L unused); then dtheta/deps
+hipError_t launch_theta_links(const geom &g, const double *U, const double *eps, double2 *L,
+                              double2 *D, double *partials, hipStream_t st);
+hipError_t launch_theta_grad(const geom &g, const double *U, const double *eps, const double2 *L,
+                             const double2 *D, double *dth, double normT, hipStream_t st);
 
 // SU(2) kernels (su2.hip); the generic launchers above dispatch to them when
 // g.nc == 2.

@@ -234,29 +234,6 @@ __global__ void __launch_bounds__(SITE_BLOCK)
     block_sum2<SITE_BLOCK>(fs, ts, partials, blockIdx.x);
 }
 
-// k_div_reduce<double, double, 2> reading the caller's AoS links directly
-// (rows 0,1; row 2 rebuilt as a 12-real load does) and storing no field.
-__global__ void __launch_bounds__(SITE_BLOCK)
-    k_measure_aos(geom g, const double2 *__restrict__ U, double *__restrict__ partials) {
-    const long s = block_site(g, blockIdx.x, gridDim.x, threadIdx.x);
-    double fs = 0, ts = 0;
-    if (s < g.V) {
-        auto link = [&](int mu, long x) {
-            mat3<double> m;
-            const double2 *u = U + ((long)mu * g.V + x) * 9;
-#pragma unroll
-            for (int k = 0; k < 6; ++k) m.e[k / 3][k % 3] = mk<double>(u[k].x, u[k].y);
-            rebuild_row2(m);
-            return m;
-        };
-        cpx<double> f[4];
-        double tr;
-        ts = divergence_at<double>(g, s, link, f, tr);
-        fs = tr;
-    }
-    block_sum2<SITE_BLOCK>(fs, ts, partials, blockIdx.x);
-}
-
 // ---------------------------------------------------------------------------
 // fused update + next divergence
 // ---------------------------------------------------------------------------
@@ -865,310 +842,6 @@ __global__ void __launch_bounds__(SITE_BLOCK)
 }
 
 // ---------------------------------------------------------------------------
-// gauge-invariant checks and F_U[g]
-// ---------------------------------------------------------------------------
-
-__global__ void __launch_bounds__(SITE_BLOCK)
-    k_plaquette(geom g, const double2 *__restrict__ L, double *__restrict__ partials) {
-    const long s = (long)blockIdx.x * SITE_BLOCK + threadIdx.x;
-    double acc = 0;
-    if (s < g.V) {
-        const nbr n = neighbours(g, s);
-#pragma unroll
-        for (int mu = 0; mu < 4; ++mu) {
-            const mat3<double> umu = load_link<double>(L, g.S, mu, s);
-#pragma unroll
-            for (int nu = mu + 1; nu < 4; ++nu) {
-                const mat3<double> a = load_link<double>(L, g.S, nu, n.p[mu]);   // U_nu(x+mu)
-                const mat3<double> b = load_link<double>(L, g.S, mu, n.p[nu]);   // U_mu(x+nu)
-                const mat3<double> c = load_link<double>(L, g.S, nu, s);         // U_nu(x)
-                // Re Tr[umu a b^+ c^+] = Re Tr[P Q^+] = Re sum_ij P_ij conj(Q_ij),
-                // P = umu a, Q = c b
-                for (int i = 0; i < 3; ++i)
-                    for (int j = 0; j < 3; ++j) {
-                        cpx<double> p = mk<double>(0, 0), q = mk<double>(0, 0);
-                        for (int k = 0; k < 3; ++k) {
-                            p = p + cmul(umu.e[i][k], a.e[k][j]);
-                            q = q + cmul(c.e[i][k], b.e[k][j]);
-                        }
-                        acc += p.re * q.re + p.im * q.im;
-                    }
-            }
-        }
-    }
-    block_sum2<SITE_BLOCK>(acc, 0.0, partials, blockIdx.x);
-}
-
-// sum_mu Re Tr[g(x) U_mu(x) g(x+mu)^dagger], g full 3x3 AoS (NULL: identity)
-__global__ void __launch_bounds__(SITE_BLOCK)
-    k_functional_g(geom g, const double2 *__restrict__ L, const double2 *__restrict__ ga,
-                   double *__restrict__ partials) {
-    const long s = (long)blockIdx.x * SITE_BLOCK + threadIdx.x;
-    double acc = 0;
-    if (s < g.V) {
-        const nbr n = neighbours(g, s);
-        mat3<double> g0;
-        for (int k = 0; k < 9; ++k) g0.e[k / 3][k % 3] = mk<double>(ga[s * 9 + k].x, ga[s * 9 + k].y);
-        for (int mu = 0; mu < 4; ++mu) {
-            mat3<double> gp;
-            const long sp = n.p[mu];
-            for (int k = 0; k < 9; ++k) gp.e[k / 3][k % 3] = mk<double>(ga[sp * 9 + k].x, ga[sp * 9 + k].y);
-            const mat3<double> u = load_link<double>(L, g.S, mu, s);
-            // Re Tr[g0 u gp^+] = Re sum_ij (g0 u)_ij conj(gp_ij)
-            for (int i = 0; i < 3; ++i)
-                for (int j = 0; j < 3; ++j) {
-                    cpx<double> p = mk<double>(0, 0);
-                    for (int k = 0; k < 3; ++k) p = p + cmul(g0.e[i][k], u.e[k][j]);
-                    acc += p.re * gp.e[i][j].re + p.im * gp.e[i][j].im;
-                }
-        }
-    }
-    block_sum2<SITE_BLOCK>(acc, 0.0, partials, blockIdx.x);
-}
-
-// ---------------------------------------------------------------------------
-// differentiation
-// ---------------------------------------------------------------------------
-
-// X = i sum_a w_a lambda_a / 2
-__device__ __forceinline__ mat3<double> su3_alg(const double *w) {
-    const double r3 = 0.57735026918962576451;  // 1/sqrt(3)
-    // H = sum_a w_a lambda_a, X = (i/2) H
-    cpx<double> H[3][3];
-    H[0][0] = mk<double>(w[2] + w[7] * r3, 0);
-    H[1][1] = mk<double>(-w[2] + w[7] * r3, 0);
-    H[2][2] = mk<double>(-2 * w[7] * r3, 0);
-    H[0][1] = mk<double>(w[0], -w[1]);
-    H[1][0] = mk<double>(w[0], w[1]);
-    H[0][2] = mk<double>(w[3], -w[4]);
-    H[2][0] = mk<double>(w[3], w[4]);
-    H[1][2] = mk<double>(w[5], -w[6]);
-    H[2][1] = mk<double>(w[5], w[6]);
-    mat3<double> X;
-    for (int i = 0; i < 3; ++i)
-        for (int j = 0; j < 3; ++j) X.e[i][j] = mk<double>(-0.5 * H[i][j].im, 0.5 * H[i][j].re);
-    return X;
-}
-
-__device__ __forceinline__ mat3<double> mat_mul_full(const mat3<double> &a, const mat3<double> &b) {
-    mat3<double> r;
-    for (int i = 0; i < 3; ++i)
-        for (int j = 0; j < 3; ++j) {
-            cpx<double> acc = cmul(a.e[i][0], b.e[0][j]);
-            acc = acc + cmul(a.e[i][1], b.e[1][j]);
-            acc = acc + cmul(a.e[i][2], b.e[2][j]);
-            r.e[i][j] = acc;
-        }
-    return r;
-}
-
-// exp(X) for anti-hermitian X: halve until |X| <= 1/2, Taylor to 24 terms, square back
-__device__ mat3<double> expm3(mat3<double> X) {
-    double nrm = 0;
-    for (int i = 0; i < 3; ++i)
-        for (int j = 0; j < 3; ++j) nrm += norm2(X.e[i][j]);
-    nrm = sqrt(nrm);
-    int sq = 0;
-    while (nrm > 0.5 && sq < 60) {
-        nrm *= 0.5;
-        ++sq;
-    }
-    const double sc = ldexp(1.0, -sq);
-    for (int i = 0; i < 3; ++i)
-        for (int j = 0; j < 3; ++j) X.e[i][j] = sc * X.e[i][j];
-    mat3<double> E, term;
-    for (int i = 0; i < 3; ++i)
-        for (int j = 0; j < 3; ++j) E.e[i][j] = term.e[i][j] = mk<double>(i == j ? 1.0 : 0.0, 0.0);
-    for (int k = 1; k <= 24; ++k) {
-        term = mat_mul_full(term, X);
-        const double inv = 1.0 / k;
-        for (int i = 0; i < 3; ++i)
-            for (int j = 0; j < 3; ++j) {
-                term.e[i][j] = inv * term.e[i][j];
-                E.e[i][j] = E.e[i][j] + term.e[i][j];
-            }
-    }
-    for (int i = 0; i < sq; ++i) E = mat_mul_full(E, E);
-    return E;
-}
-
-__global__ void k_expm_sites(const double *__restrict__ w, double2 *__restrict__ out, long n) {
-    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    double ww[8];
-    for (int a = 0; a < 8; ++a) ww[a] = w[i * 8 + a];
-    const mat3<double> E = expm3(su3_alg(ww));
-    for (int k = 0; k < 9; ++k) out[i * 9 + k] = make_double2(E.e[k / 3][k % 3].re, E.e[k / 3][k % 3].im);
-}
-
-__device__ __forceinline__ mat3<double> load_full(const double2 *__restrict__ a, long i) {
-    mat3<double> m;
-    for (int k = 0; k < 9; ++k) m.e[k / 3][k % 3] = mk<double>(a[i * 9 + k].x, a[i * 9 + k].y);
-    return m;
-}
-
-// links Lout_mu(x) = g(x) Lin_mu(x) g(x+mu)^dagger (g full AoS, unitary)
-__global__ void __launch_bounds__(SITE_BLOCK)
-    k_rotate_links(geom g, const double2 *__restrict__ Lin, const double2 *__restrict__ ga,
-                   double2 *__restrict__ Lout) {
-    const long s = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= g.V) return;
-    const nbr n = neighbours(g, s);
-    const mat3<double> g0 = load_full(ga, s);
-    for (int mu = 0; mu < 4; ++mu) {
-        const mat3<double> gp = load_full(ga, n.p[mu]);
-        const mat3<double> u = load_link<double>(Lin, g.S, mu, s);
-        store_link<double>(Lout, g.S, mu, s, mul_abcd(g0, u, gp));
-    }
-}
-
-// Lout_mu(x) = E_mu(x) Lin_mu(x), E full AoS [4][V]
-__global__ void k_left_multiply(const double2 *__restrict__ Lin, const double2 *__restrict__ E,
-                                double2 *__restrict__ Lout, long V, long S) {
-    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= 4 * V) return;
-    const int mu = (int)(i / V);
-    const long s = i - (long)mu * V;
-    const mat3<double> e = load_full(E, i);
-    const mat3<double> u = load_link<double>(Lin, S, mu, s);
-    mat3<double> r = mat_mul_full(e, u);
-    store_link<double>(Lout, S, mu, s, r);
-}
-
-// Im Tr[lambda_a W], a = 0..7
-__device__ __forceinline__ void im_tr_lambda(const mat3<double> &W, double y[8]) {
-    const double r3 = 0.57735026918962576451;
-    y[0] = W.e[1][0].im + W.e[0][1].im;
-    y[1] = W.e[0][1].re - W.e[1][0].re;
-    y[2] = W.e[0][0].im - W.e[1][1].im;
-    y[3] = W.e[2][0].im + W.e[0][2].im;
-    y[4] = W.e[0][2].re - W.e[2][0].re;
-    y[5] = W.e[2][1].im + W.e[1][2].im;
-    y[6] = W.e[1][2].re - W.e[2][1].re;
-    y[7] = (W.e[0][0].im + W.e[1][1].im - 2 * W.e[2][2].im) * r3;
-}
-
-// out = sum_k (A^T)^k v / (k+1)!,  A[b][a] = coefficient of i T^b in [i w.T, i T^a]
-//     = -sum_c f_abc w_c  (SU(3) structure constants).
-// This is the transpose of the derivative of the exponential map, so for
-// g = exp(i w.T): d/dw^a = sum_b S[b][a] (derivative along i T^b g).
-__device__ void dexp_transpose_apply(const double *w, const double *v, double *out) {
-    double A[8][8];
-    for (int i = 0; i < 8; ++i)
-        for (int j = 0; j < 8; ++j) A[i][j] = 0;
-    const int tri[9][3] = {{0, 1, 2}, {0, 3, 6}, {0, 5, 4}, {1, 3, 5}, {1, 4, 6},
-                           {2, 3, 4}, {2, 6, 5}, {3, 4, 7}, {5, 6, 7}};
-    const double h3 = 0.86602540378443864676;
-    const double fv[9] = {1.0, 0.5, 0.5, 0.5, 0.5, 0.5, 0.5, h3, h3};
-    for (int t = 0; t < 9; ++t) {
-        const int a = tri[t][0], b = tri[t][1], c = tri[t][2];
-        const double v0 = fv[t];
-        // f_ijk w_k contributes -f_ijk w_k to A[j][i] for every permutation (i,j,k)
-        A[b][a] -= v0 * w[c];  // (a,b,c) +
-        A[c][b] -= v0 * w[a];  // (b,c,a) +
-        A[a][c] -= v0 * w[b];  // (c,a,b) +
-        A[a][b] += v0 * w[c];  // (b,a,c) -
-        A[c][a] += v0 * w[b];  // (a,c,b) -
-        A[b][c] += v0 * w[a];  // (c,b,a) -
-    }
-    double term[8], acc[8];
-    for (int i = 0; i < 8; ++i) term[i] = acc[i] = v[i];
-    for (int k = 1; k <= 80; ++k) {
-        double nt[8];
-        double mx = 0;
-        for (int a = 0; a < 8; ++a) {
-            double s = 0;
-            for (int b = 0; b < 8; ++b) s += A[b][a] * term[b];
-            nt[a] = s / (k + 1);
-            mx = fmax(mx, fabs(nt[a]));
-        }
-        double ma = 0;
-        for (int a = 0; a < 8; ++a) {
-            term[a] = nt[a];
-            acc[a] += nt[a];
-            ma = fmax(ma, fabs(acc[a]));
-        }
-        if (mx <= 1e-18 * ma) break;
-    }
-    for (int a = 0; a < 8; ++a) out[a] = acc[a];
-}
-
-// dF/domega from Delta of the transformed links (D64 fields) and omega
-__global__ void k_omega_grad(geom g, const double2 *__restrict__ D, const double *__restrict__ om,
-                             double *__restrict__ dF, double normF) {
-    const long s = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= g.V) return;
-    const double2 f0 = D[s], f1 = D[g.S + s], f2 = D[2 * g.S + s], f3 = D[3 * g.S + s];
-    mat3<double> M;
-    M.e[0][0] = mk<double>(0, f3.x);
-    M.e[0][1] = mk<double>(f0.x, f0.y);
-    M.e[0][2] = mk<double>(f1.x, f1.y);
-    M.e[1][0] = mk<double>(-f0.x, f0.y);
-    M.e[1][1] = mk<double>(0, f3.y);
-    M.e[1][2] = mk<double>(f2.x, f2.y);
-    M.e[2][0] = mk<double>(-f1.x, f1.y);
-    M.e[2][1] = mk<double>(-f2.x, f2.y);
-    M.e[2][2] = mk<double>(0, -(f3.x + f3.y));
-    double y[8], G[8], w[8], out[8];
-    im_tr_lambda(M, y);
-    // G^b = -(i/4) normF Tr[lambda_b Delta] = (normF/4) Im Tr[lambda_b Delta]
-    for (int b = 0; b < 8; ++b) G[b] = 0.25 * normF * y[b];
-    for (int a = 0; a < 8; ++a) w[a] = om[s * 8 + a];
-    dexp_transpose_apply(w, G, out);
-    for (int a = 0; a < 8; ++a) dF[s * 8 + a] = out[a];
-}
-
-// dtheta/deps^a_mu(x) at links L (already exp(i eps.T) U); eps may be NULL
-__global__ void __launch_bounds__(SITE_BLOCK)
-    k_theta_grad(geom g, const double2 *__restrict__ L, const double2 *__restrict__ D,
-                 const double *__restrict__ eps, double *__restrict__ dth, double normT) {
-    const long s = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= g.V) return;
-    const nbr n = neighbours(g, s);
-    auto fieldmat = [&](long q) {
-        const double2 f0 = D[q], f1 = D[g.S + q], f2 = D[2 * g.S + q], f3 = D[3 * g.S + q];
-        mat3<double> M;
-        M.e[0][0] = mk<double>(0, f3.x);
-        M.e[0][1] = mk<double>(f0.x, f0.y);
-        M.e[0][2] = mk<double>(f1.x, f1.y);
-        M.e[1][0] = mk<double>(-f0.x, f0.y);
-        M.e[1][1] = mk<double>(0, f3.y);
-        M.e[1][2] = mk<double>(f2.x, f2.y);
-        M.e[2][0] = mk<double>(-f1.x, f1.y);
-        M.e[2][1] = mk<double>(-f2.x, f2.y);
-        M.e[2][2] = mk<double>(0, -(f3.x + f3.y));
-        return M;
-    };
-    const mat3<double> d0 = fieldmat(s);
-    for (int mu = 0; mu < 4; ++mu) {
-        const mat3<double> dp = fieldmat(n.p[mu]);
-        mat3<double> Dd;
-        for (int i = 0; i < 3; ++i)
-            for (int j = 0; j < 3; ++j) Dd.e[i][j] = dp.e[i][j] - d0.e[i][j];
-        const mat3<double> u = load_link<double>(L, g.S, mu, s);
-        mat3<double> ud;
-        for (int i = 0; i < 3; ++i)
-            for (int j = 0; j < 3; ++j) ud.e[i][j] = conjg(u.e[j][i]);
-        const mat3<double> W1 = mat_mul_full(u, Dd), W2 = mat_mul_full(Dd, ud);
-        mat3<double> W;
-        for (int i = 0; i < 3; ++i)
-            for (int j = 0; j < 3; ++j) W.e[i][j] = W1.e[i][j] + W2.e[i][j];
-        double y[8], out[8];
-        im_tr_lambda(W, y);
-        for (int a = 0; a < 8; ++a) y[a] *= normT;
-        const long o = ((long)mu * g.V + s) * 8;
-        if (eps) {
-            double w[8];
-            for (int a = 0; a < 8; ++a) w[a] = eps[o + a];
-            dexp_transpose_apply(w, y, out);
-        } else {
-            for (int a = 0; a < 8; ++a) out[a] = y[a];
-        }
-        for (int a = 0; a < 8; ++a) dth[o + a] = out[a];
-    }
-}
-
-// ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
 
@@ -1400,11 +1073,9 @@ hipError_t launch_reduce_only(const double *partials, int nparts, double *out2, 
     return hipGetLastError();
 }
 
-hipError_t launch_measure_aos(const geom &g, const double *Uaos, double *partials, double *out,
-                              double normF, double normT, hipStream_t st) {
-    const int nb = site_blocks(g.V);
-    k_measure_aos<<<nb, SITE_BLOCK, 0, st>>>(g, reinterpret_cast<const double2 *>(Uaos), partials);
-    k_measure_finalize<<<1, FIN_BLOCK, 0, st>>>(partials, nb, out, normF, normT);
+hipError_t launch_measure_finalize(const double *partials, int nparts, double *out, double normF,
+                                   double normT, hipStream_t st) {
+    k_measure_finalize<<<1, FIN_BLOCK, 0, st>>>(partials, nparts, out, normF, normT);
     return hipGetLastError();
 }
 
@@ -1458,54 +1129,6 @@ hipError_t launch_field_from_matrix(const double *Maos, void *D64, long V, long 
 hipError_t launch_matrix_from_field(const void *D64, double *Maos, long V, long S, hipStream_t st) {
     k_matrix_from_field<<<nblk(V, 256), 256, 0, st>>>(static_cast<const double2 *>(D64),
                                                       reinterpret_cast<double2 *>(Maos), V, S);
-    return hipGetLastError();
-}
-
-hipError_t launch_plaquette(const geom &g, const void *L64, double *partials, hipStream_t st) {
-    k_plaquette<<<site_blocks(g.V), SITE_BLOCK, 0, st>>>(g, static_cast<const double2 *>(L64),
-                                                         partials);
-    return hipGetLastError();
-}
-
-hipError_t launch_functional_g(const geom &g, const void *L64, const double *gaos,
-                               double *partials, hipStream_t st) {
-    k_functional_g<<<site_blocks(g.V), SITE_BLOCK, 0, st>>>(
-        g, static_cast<const double2 *>(L64), reinterpret_cast<const double2 *>(gaos), partials);
-    return hipGetLastError();
-}
-
-hipError_t launch_expm_sites(const double *omega, double *gaos, long n, hipStream_t st) {
-    k_expm_sites<<<nblk(n, 128), 128, 0, st>>>(omega, reinterpret_cast<double2 *>(gaos), n);
-    return hipGetLastError();
-}
-
-hipError_t launch_rotate_links(const geom &g, const void *Lin, const double *gaos, void *Lout,
-                               hipStream_t st) {
-    k_rotate_links<<<site_blocks(g.V), SITE_BLOCK, 0, st>>>(
-        g, static_cast<const double2 *>(Lin), reinterpret_cast<const double2 *>(gaos),
-        static_cast<double2 *>(Lout));
-    return hipGetLastError();
-}
-
-hipError_t launch_left_multiply_links(const void *Lin, const double *eaos, void *Lout, long V,
-                                      long S, hipStream_t st) {
-    k_left_multiply<<<nblk(4 * V, 256), 256, 0, st>>>(static_cast<const double2 *>(Lin),
-                                                      reinterpret_cast<const double2 *>(eaos),
-                                                      static_cast<double2 *>(Lout), V, S);
-    return hipGetLastError();
-}
-
-hipError_t launch_omega_grad(const geom &g, const void *D64, const double *omega, double *dF,
-                             double normF, hipStream_t st) {
-    k_omega_grad<<<nblk(g.V, 128), 128, 0, st>>>(g, static_cast<const double2 *>(D64), omega, dF,
-                                                 normF);
-    return hipGetLastError();
-}
-
-hipError_t launch_theta_grad(const geom &g, const void *L64, const void *D64, const double *eps,
-                             double *dth, double normT, hipStream_t st) {
-    k_theta_grad<<<site_blocks(g.V), SITE_BLOCK, 0, st>>>(
-        g, static_cast<const double2 *>(L64), static_cast<const double2 *>(D64), eps, dth, normT);
     return hipGetLastError();
 }
 
