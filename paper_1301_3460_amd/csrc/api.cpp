@@ -60,10 +60,13 @@ struct lgf_ctx {
     double *pt64 = nullptr;
     float *pt32 = nullptr;
     fft_plan plan64{}, plan32{};  // how the transform is split into passes
+    small_plan small64{}, small32{};  // or is done by one block per field
     // reductions and control
     double *partials = nullptr;
     int nparts = 0;
-    dev_status *status = nullptr;
+    // the current state, one of two slots: a small lattice's transform reads one
+    // and writes the other (launch_fft4_small)
+    dev_status *status = nullptr, *status_slots = nullptr;
     dev_status *status_host = nullptr;  // pinned, 3 slots: synchronous reads, two batches
     hipEvent_t batch_ev[2] = {nullptr, nullptr};  // a batch's status copy has landed
     double *reduce_out = nullptr;       // device [2]
@@ -189,6 +192,16 @@ float2 *acc_G(lgf_ctx *c, int n) { return (c->g.nc == 3 && (n & 1)) ? c->L32[1] 
 // does not need (after a hand-over the FP32 copies there are dead).
 double2 *acc_G64(lgf_ctx *c, int n) { return c->L64[1] + (n & 1) * 6 * c->g.S; }
 
+// FP64 sweeps that store their links take the small-lattice update
+bool use_dirs(const lgf_ctx *c) {
+    return c->g.nc == 3 && c->g.lf == 12 && c->g.V <= UPDATE_DIRS_MAX_SITES;
+}
+
+// Pairs of partials the update of a sweep in precision T writes
+template <class T> int update_parts(const lgf_ctx *c) {
+    return std::is_same<T, double>::value && use_dirs(c) ? update_dirs_parts(c->g) : c->nparts;
+}
+
 // Arguments of launch_update for the sweep from buffer `cur` into `cur^1`.
 template <class T>
 hipError_t sweep_update(lgf_ctx *c, int cur, void *D, T half_alpha, const fin_params &fp) {
@@ -202,6 +215,10 @@ hipError_t sweep_update(lgf_ctx *c, int cur, void *D, T half_alpha, const fin_pa
         if (c->g.keeps_u0())
             return launch_update_u0(c->g, c->L64[0], acc_G64(c, cur ^ 1), P::field(c, cur ^ 1),
                                     c->partials, c->status, fp, c->stream);
+        if (use_dirs(c))
+            return launch_update_dirs(c->g, c->L64[cur], c->L64[cur ^ 1], D, P::field(c, cur ^ 1),
+                                      half_alpha, c->exact_exp, c->Gex, c->partials, c->status, fp,
+                                      c->stream);
     }
     return launch_update<T>(c->g, P::links(c, cur), P::links(c, cur ^ 1), D, P::field(c, cur ^ 1),
                             std::is_same<T, float>::value ? c->G32 : nullptr, half_alpha,
@@ -274,17 +291,65 @@ hipError_t sweep_pass(lgf_ctx *c, int n, void *D, int pass) {
     return transform_pass(c, field32<T>(c), pass, D);
 }
 
+template <class T> bool use_small(const lgf_ctx *c) {
+    return c->accelerate && (field32<T>(c) ? c->small32.on : c->small64.on);
+}
+
+// The first kernel of a sweep's transform can take the stopping test of the
+// sweep before along (a few hundred partials, summed by every wave).
+template <class T> bool use_fold(const lgf_ctx *c) {
+    return c->accelerate && update_parts<T>(c) <= FOLD_MAX_PARTS &&
+           (use_small<T>(c) || fft_xy_folds(field32<T>(c) ? c->plan32 : c->plan64));
+}
+
 // Sweep n (counted from the phase's first, 0) from links/field buffer n & 1
-// into the other one.
+// into the other one.  first, last: the batch's first sweep, and its last,
+// which always has its own stopping test.
 template <class T>
-hipError_t enqueue_sweep(lgf_ctx *c, int n, T half_alpha, const fin_params &fp) {
+hipError_t enqueue_sweep(lgf_ctx *c, int n, T half_alpha, const fin_params &fp, bool first,
+                         bool last) {
     using P = prec<T>;
     hipError_t e;
     const int cur = n & 1;
     void *D = P::field(c, cur);
-    for (int pass = 0; pass < 3; ++pass)
-        if ((e = sweep_pass<T>(c, n, D, pass)) != hipSuccess) return e;
-    return sweep_update<T>(c, cur, D, half_alpha, fp);
+    const bool fold = use_fold<T>(c), f32 = field32<T>(c);
+    fold_args fa;
+    const dev_status *before = c->status;
+    if (fold && !first) {
+        fa.partials = c->partials;
+        fa.nparts = update_parts<T>(c);
+        fa.fp = fp;
+        fa.out = c->status_slots + (c->status == c->status_slots);
+        c->status = fa.out;  // what the kernels after the first one read
+    }
+    if (use_small<T>(c)) {
+        const double k = c->p2max / (double)c->g.V;
+        e = f32 ? launch_fft4_small<float>(c->g, D, c->tw32, c->pt32, (float)k, c->small32, before,
+                                           fa, c->stream)
+                : launch_fft4_small<double>(c->g, D, c->tw64, c->pt64, k, c->small64, before, fa,
+                                            c->stream);
+        if (e != hipSuccess) return e;
+        // G <- g G of the sweeps that keep U0 and G
+        if (std::is_same<T, float>::value && c->g.nc == 3) {
+            e = launch_gauge_acc<float, float>(c->g, D, n ? acc_G(c, cur) : nullptr,
+                                               acc_G(c, cur ^ 1), c->half_alpha, c->exact_exp,
+                                               c->status, c->stream);
+            if (e != hipSuccess) return e;
+        }
+    } else {
+        int pass = 0;
+        if (fa.fp.enabled) {
+            e = f32 ? launch_fft_xy<float>(c->g, D, -1, c->tw32, c->plan32, before, c->stream, fa)
+                    : launch_fft_xy<double>(c->g, D, -1, c->tw64, c->plan64, before, c->stream, fa);
+            if (e != hipSuccess) return e;
+            pass = 1;
+        }
+        for (; pass < 3; ++pass)
+            if ((e = sweep_pass<T>(c, n, D, pass)) != hipSuccess) return e;
+    }
+    fin_params test = fp;
+    if (fold && !last) test.enabled = 0;
+    return sweep_update<T>(c, cur, D, half_alpha, test);
 }
 
 int read_status(lgf_ctx *c, dev_status &out) {
@@ -301,10 +366,12 @@ int read_status(lgf_ctx *c, dev_status &out) {
 // prepared: the status reset and the first divergence with its stopping test
 // were enqueued by the caller (the mixed hand-over fuses them).
 //
-// Sweeps go to the stream in batches.  After each batch the device status is
-// copied to a pinned host slot (two slots, alternating, each with an event),
-// and the next batch is enqueued before the host waits for the previous
-// one's status, so the device does not idle while the host decides: a solve
+// Sweeps go to the stream in batches.  The last stopping test of a batch
+// writes the state to a pinned host slot (two slots, alternating, each with an
+// event), and the next batch is enqueued before the host waits for the
+// previous one's state, so the device does not idle while the host decides
+// (nor before the first batch, whose sweeps do nothing where the links are
+// fixed already, nor after the last): a solve
 // sizes each batch from the contraction rate last observed, counting the
 // sweeps still in flight; once the stopping test has fired, sweeps still in
 // flight find the device flag set and return at once.  A fixed count of
@@ -318,14 +385,14 @@ int run_phase(lgf_ctx *c, double alpha, double tol, int max_iter, int hist_base,
                                        c->partials, c->status,
                                        finp(c, true, tol, max_iter, 0, stall), c->stream));
     }
-    int rc = read_status(c, st);
-    if (rc) return rc;
     const T half_alpha = (T)(0.5 * alpha);
     c->half_alpha = 0.5 * alpha;
     const fin_params fp = finp(c, true, tol, max_iter, 1, stall);
+    int rc = LGF_OK;
     int enq = 0;              // sweeps enqueued so far
-    double th_prev = st.theta;  // the observation before the last one (rate)
-    int n_prev = st.n;
+    st = dev_status{};        // the last observed state (none yet)
+    double th_prev = 0;       // the observation before the last one (rate)
+    int n_prev = 0;
     // sweeps to enqueue next, from the last observed state and the sweeps
     // enqueued beyond it.  A solve caps its batches at max(4, n/8): the
     // contraction rate of the accelerated method rises several-fold in its
@@ -346,11 +413,12 @@ int run_phase(lgf_ctx *c, double alpha, double tol, int max_iter, int hist_base,
     };
     auto enqueue_batch = [&](int k, int slot) -> int {
         for (int i = 0; i < k; ++i) {
-            HIPCHK(c, enqueue_sweep<T>(c, enq + i, half_alpha, fp));
+            const bool last = i == k - 1;
+            fin_params f = fp;
+            if (last) f.host = c->status_host + 1 + slot;
+            HIPCHK(c, enqueue_sweep<T>(c, enq + i, half_alpha, f, i == 0, last));
         }
         enq += k;
-        HIPCHK(c, hipMemcpyAsync(c->status_host + 1 + slot, c->status, sizeof(dev_status),
-                                 hipMemcpyDeviceToHost, c->stream));
         HIPCHK(c, hipEventRecord(c->batch_ev[slot], c->stream));
         return LGF_OK;
     };
@@ -381,8 +449,6 @@ int run_phase(lgf_ctx *c, double alpha, double tol, int max_iter, int hist_base,
         st = c->status_host[1 + (observed & 1)];
         ++observed;
     }
-    // sweeps enqueued after the stop return at once; let them drain
-    HIPCHK(c, hipStreamSynchronize(c->stream));
     return LGF_OK;
 }
 
@@ -491,7 +557,7 @@ int profile_impl(lgf_ctx *c, const double *U, double alpha, int n, double *ms) {
         chk(hipEventRecord(e[3], c->stream));
         chk(sweep_update<T>(c, cur, D, half_alpha, finp(c, false)));
         chk(hipEventRecord(e[4], c->stream));
-        chk(launch_finalize(c->partials, c->nparts, c->status, finp(c, true, 0.0, n + 1, 1),
+        chk(launch_finalize(c->partials, update_parts<T>(c), c->status, finp(c, true, 0.0, n + 1, 1),
                             c->stream));
         chk(hipEventRecord(e[5], c->stream));
         if (err != hipSuccess) rc = fail(c, LGF_ERR_DEVICE, hipGetErrorString(err));
@@ -548,6 +614,7 @@ int noalloc_scratch(double **out) {
 }  // namespace
 
 namespace lgf {
+bool fft_xy_folds(const fft_plan &p) { return p.t2 || (!p.xy2 && p.xy != 2); }
 bool fft_plan_fits(const fft_plan &p) {
     constexpr size_t LDS_MAX = 160 * 1024;
     auto axis_ok = [&](const axis_plan &a) {
@@ -611,8 +678,10 @@ int lgf_create_group(lgf_ctx **out, const int L[4], int nc, int precision, void 
     ok = ok && alloc((void **)&c->tw32, nt * sizeof(float2));
     ok = ok && alloc((void **)&c->pt64, nt * sizeof(double));
     ok = ok && alloc((void **)&c->pt32, nt * sizeof(float));
-    ok = ok && alloc((void **)&c->partials, (size_t)2 * c->nparts * sizeof(double));
-    ok = ok && alloc((void **)&c->status, sizeof(dev_status));
+    ok = ok && alloc((void **)&c->partials,
+                     (size_t)2 * std::max(c->nparts, use_dirs(c) ? update_dirs_parts(c->g) : 0) * sizeof(double));
+    ok = ok && alloc((void **)&c->status_slots, 2 * sizeof(dev_status));
+    c->status = c->status_slots;
     ok = ok && alloc((void **)&c->reduce_out, 2 * sizeof(double));
     ok = ok && alloc((void **)&c->histF, HIST_CAP * sizeof(double));
     ok = ok && alloc((void **)&c->histT, HIST_CAP * sizeof(double));
@@ -646,6 +715,10 @@ int lgf_create_group(lgf_ctx **out, const int L[4], int nc, int precision, void 
     fft_set_max_lds<double>(c->g, c->plan64);
     fft_set_max_lds<float>(c->g, c->plan32);
     update_set_max_lds();
+    c->small64 = plan_small<double>(c->g, c->plan64);
+    c->small32 = plan_small<float>(c->g, c->plan32);
+    small_set_max_lds<double>(c->small64);
+    small_set_max_lds<float>(c->small32);
     if (e != hipSuccess) {
         std::string m = std::string("initialisation failed: ") + hipGetErrorString(e);
         lgf_destroy(c);
@@ -661,7 +734,7 @@ void lgf_destroy(lgf_ctx *c) {
     if (c->stream) (void)hipStreamSynchronize(c->stream);
     else (void)hipDeviceSynchronize();
     void *dev[] = {c->L64[0], c->L64[1], c->D64[0], c->D64[1], c->G32, c->tw64, c->tw32,
-                   c->pt64, c->pt32, c->partials, c->status, c->reduce_out, c->histF, c->histT,
+                   c->pt64, c->pt32, c->partials, c->status_slots, c->reduce_out, c->histF, c->histT,
                    c->Gex};
     for (void *p : dev)
         if (p) (void)hipFree(p);

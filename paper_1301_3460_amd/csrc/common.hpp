@@ -102,4 +102,163 @@ __device__ __forceinline__ void block_sum2(double a, double b, double *partials,
     }
 }
 
+// ---------------------------------------------------------------------------
+// fixed-order sum of block partials and the stopping test
+// ---------------------------------------------------------------------------
+
+template <int NT>
+__device__ __forceinline__ void fixed_order_sum(const double *__restrict__ partials, int nparts,
+                                                double &A, double &B) {
+    // thread t adds pairs t, t + NT, t + 2 NT, ... in that order; four 16-byte
+    // loads are in flight per step
+    const double2 *p2 = reinterpret_cast<const double2 *>(partials);
+    double a = 0, b = 0;
+    int i = threadIdx.x;
+    for (; i + 3 * NT < nparts; i += 4 * NT) {
+        const double2 v0 = p2[i], v1 = p2[i + NT], v2 = p2[i + 2 * NT], v3 = p2[i + 3 * NT];
+        a += v0.x;
+        b += v0.y;
+        a += v1.x;
+        b += v1.y;
+        a += v2.x;
+        b += v2.y;
+        a += v3.x;
+        b += v3.y;
+    }
+    for (; i < nparts; i += NT) {
+        const double2 v = p2[i];
+        a += v.x;
+        b += v.y;
+    }
+    __shared__ double sa[NT], sb[NT];
+    sa[threadIdx.x] = a;
+    sb[threadIdx.x] = b;
+    __syncthreads();
+    for (int h = NT / 2; h > 0; h >>= 1) {
+        if (threadIdx.x < h) {
+            sa[threadIdx.x] += sa[threadIdx.x + h];
+            sb[threadIdx.x] += sb[threadIdx.x + h];
+        }
+        __syncthreads();
+    }
+    A = sa[0];
+    B = sb[0];
+}
+
+// The same without a block-wide tree: lane l of a wave adds pairs l, l + n, ...
+// (n lanes), then the lanes are added pairwise.  Blocks of whole waves do it in
+// every wave, without LDS or barriers; other blocks in their first wave.  For
+// a few hundred pairs; the same value in every thread of every block of a
+// launch.
+__device__ __forceinline__ void wave_sum(const double *__restrict__ partials, int nparts, double &A,
+                                         double &B) {
+    const double2 *p2 = reinterpret_cast<const double2 *>(partials);
+    const int lane = threadIdx.x & 63;
+    const bool whole = blockDim.x % 64 == 0;
+    const int n = whole ? 64 : min(64u, blockDim.x);
+    double a = 0, b = 0;
+    if (whole || threadIdx.x < 64) {
+        for (int i = lane; i < nparts; i += n) {
+            const double2 v = p2[i];
+            a += v.x;
+            b += v.y;
+        }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+            const double u = __shfl_down(a, off), v = __shfl_down(b, off);
+            if (lane + off < n) {
+                a += u;
+                b += v;
+            }
+        }
+        a = __shfl(a, 0);
+        b = __shfl(b, 0);
+    }
+    if (!whole && blockDim.x > 64) {
+        __shared__ double ab[2];
+        if (threadIdx.x == 0) {
+            ab[0] = a;
+            ab[1] = b;
+        }
+        __syncthreads();
+        a = ab[0];
+        b = ab[1];
+    }
+    A = a;
+    B = b;
+}
+
+// The state after a sweep whose partials sum to A and B: F = A normF, theta =
+// B normT, and the stopping test.  write_hist: also the history (one thread).
+__device__ __forceinline__ dev_status next_state(double A, double B, dev_status st,
+                                                 const fin_params &fp, bool write_hist = true) {
+    const double F = A * fp.normF, th = B * fp.normT;
+    if (fp.increment) st.n += 1;
+    const int h = st.hist_base + st.n;
+    if (write_hist && h < fp.hist_cap) {
+        fp.histF[h] = F;
+        fp.histT[h] = th;
+    }
+    st.F = F;
+    st.theta = th;
+    if (!isfinite(th) || !isfinite(F)) {
+        st.done = 1;
+        st.code = ST_NONFINITE;
+    } else if (th < fp.tol) {
+        st.done = 1;
+        st.code = ST_CONVERGED;
+    } else if (st.n >= fp.max_iter) {
+        st.done = 1;
+        st.code = ST_MAXITER;
+    } else if (fp.tol > 0) {
+        // a solve (tol > 0) also stops when theta diverges or stalls; a fixed
+        // count of sweeps (tol == 0) runs them all
+        st.rises = (st.n > 0 && th > st.theta_prev) ? st.rises + 1 : 0;
+        st.since_min = (st.n == 0 || th < st.theta_min) ? 0 : st.since_min + 1;
+        if (st.rises >= DIVERGE_RISES && th > DIVERGE_GROWTH * st.theta_min) {
+            st.done = 1;
+            st.code = ST_DIVERGING;
+        } else if (fp.stall > 0 && st.since_min >= fp.stall) {
+            st.done = 1;
+            st.code = ST_STALLED;
+        }
+    }
+    st.theta_prev = th;
+    st.theta_min = (st.n == 0 || th < st.theta_min) ? th : st.theta_min;
+    return st;
+}
+
+// The start of a sweep's first kernel: whether the sweeps are over, with the
+// stopping test of the sweep before if fold asks for it (every wave sums the
+// partials; the grid's first thread writes the state).
+__device__ __forceinline__ bool sweeps_over(const dev_status *__restrict__ status,
+                                            const fold_args &fold) {
+    if (!fold.fp.enabled) return status->done != 0;
+    const bool first = (threadIdx.x | blockIdx.x | blockIdx.y | blockIdx.z) == 0;
+    const dev_status st = *status;
+    if (st.done) {
+        if (first) *fold.out = st;
+        return true;
+    }
+    double A, B;
+    wave_sum(fold.partials, fold.nparts, A, B);
+    const dev_status nx = next_state(A, B, st, fold.fp, first);
+    if (first) *fold.out = nx;
+    return nx.done != 0;
+}
+
+// Lattices whose sweep kernels load their tiles before they look at the state
+// (see discard): where a launch is a few microseconds, the state's latency is
+// a good part of it; where it is not, a sweep enqueued past the stop should
+// return without reading its field.
+__device__ __forceinline__ bool tiles_first(const geom &g) { return g.V <= 163840; }
+
+// A use of loaded values on the path that returns without them: it keeps the
+// loads above the branch, so that their latency overlaps that of the state the
+// branch depends on.
+template <class T, int N> __device__ __forceinline__ void discard(const cpx<T> (&a)[N]) {
+#pragma unroll
+    for (int j = 0; j < N; ++j) asm volatile("" ::"v"(a[j].re), "v"(a[j].im));
+}
+
 }  // namespace lgf

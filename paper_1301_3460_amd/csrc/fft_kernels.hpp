@@ -118,8 +118,8 @@ constexpr size_t XY_PLANE_LDS_MAX = 160 * 1024;
 template <class T, int DIR, int RMAX>
 __global__ void __launch_bounds__(XY_BLOCK)
     k_fft_xy(geom g, vec2_t<T> *__restrict__ D, const vec2_t<T> *__restrict__ tw,
-             const dev_status *__restrict__ status) {
-    if (status->done) return;
+             const dev_status *__restrict__ status, fold_args fold) {
+    if (DIR < 0 ? sweeps_over(status, fold) : status->done != 0) return;
     extern __shared__ unsigned char smem_raw[];
     vec2_t<T> *lds = reinterpret_cast<vec2_t<T> *>(smem_raw);
     const int Lx = g.Lx, Ly = g.Ly, P = Lx + 1;
@@ -300,8 +300,8 @@ template <class T, int MODE, int RMAX, int NTHR>
 __global__ void __launch_bounds__(NTHR)
     k_fft_tile2(geom g, vec2_t<T> *__restrict__ D, const vec2_t<T> *__restrict__ tw,
                 const T *__restrict__ ptab, T p2max_over_V, tile2_plan tp,
-                const dev_status *__restrict__ status) {
-    if (status->done) return;
+                const dev_status *__restrict__ status, fold_args fold) {
+    if (MODE < 0 ? sweeps_over(status, fold) : status->done != 0) return;
     extern __shared__ unsigned char smem_raw[];
     vec2_t<T> *lds = reinterpret_cast<vec2_t<T> *>(smem_raw);
     // inner groups of one outer slice are consecutive on one XCD (they share lines)
@@ -500,8 +500,7 @@ template <class T> constexpr int rc_max_threads() { return sizeof(T) == 8 ? 256 
 template <class T, int NY, int DIR>
 __global__ void __launch_bounds__(rc_max_threads<T>())
     k_fft_xy_rc(geom g, vec2_t<T> *__restrict__ D, const vec2_t<T> *__restrict__ tw, int F,
-                const dev_status *__restrict__ status) {
-    if (status->done) return;
+                const dev_status *__restrict__ status, fold_args fold) {
     extern __shared__ unsigned char smem_raw[];
     vec2_t<T> *lds = reinterpret_cast<vec2_t<T> *>(smem_raw);
     const int Lx = g.Lx;
@@ -511,9 +510,11 @@ __global__ void __launch_bounds__(rc_max_threads<T>())
     const int SW = Lx + 1, PJ = F * SW;
     const vec2_t<T> *twy = tw_y<T>(g, tw);
     vec2_t<T> *p = D + (long)f * g.S + (long)blockIdx.x * Lxy + x;
+    if (!tiles_first(g) && status->done) return;
     cpx<T> a[NY];
 #pragma unroll
     for (int y = 0; y < NY; ++y) a[y] = ld<T>(p + (long)y * Lx);
+    if (DIR < 0 ? sweeps_over(status, fold) : status->done != 0) return discard(a);
     auto base = [F, SW, PJ](int c) { return (c / F) * PJ + (c % F) * SW; };  // c = fl + F*j
     auto col = [&](int, int C) { col_fft_small<DIR, T>(Lx, lds, F * C, 1, base, tw); };
     if (DIR < 0) {
@@ -538,7 +539,6 @@ __global__ void __launch_bounds__(rc_max_threads<T>())
     k_fft_xy_rc_acc(geom g, const vec2_t<T> *__restrict__ D, const vec2_t<T> *__restrict__ tw,
                     const vec2_t<TG> *__restrict__ Gold, vec2_t<TG> *__restrict__ Gnew, double c,
                     const dev_status *__restrict__ status) {
-    if (status->done) return;
     extern __shared__ unsigned char smem_raw[];
     vec2_t<T> *lds = reinterpret_cast<vec2_t<T> *>(smem_raw);
     constexpr int F = 4;
@@ -547,9 +547,11 @@ __global__ void __launch_bounds__(rc_max_threads<T>())
     const int x = threadIdx.x % Lx, fl = threadIdx.x / Lx;
     const int SW = Lx + 1, PJ = F * SW;
     const vec2_t<T> *p = D + (long)fl * g.S + (long)blockIdx.x * Lxy + x;
+    if (!tiles_first(g) && status->done) return;
     cpx<T> a[NY];
 #pragma unroll
     for (int y = 0; y < NY; ++y) a[y] = ld<T>(p + (long)y * Lx);
+    if (status->done) return discard(a);
     auto base = [SW, PJ](int cc) { return (cc / F) * PJ + (cc % F) * SW; };  // cc = fl + F*j
     auto col = [&](int, int C) { col_fft_small<+1, T>(Lx, lds, F * C, 1, base, tw); };
     exchange_axis<NY, T>(a, fl, x, 1, SW, PJ, lds, col);
@@ -574,7 +576,6 @@ __global__ void __launch_bounds__(rc_max_threads<T>())
     k_fft_zt_rc(geom g, vec2_t<T> *__restrict__ D, const vec2_t<T> *__restrict__ tw,
                 const T *__restrict__ ptab, T p2max_over_V, int W,
                 const dev_status *__restrict__ status) {
-    if (status->done) return;
     extern __shared__ unsigned char smem_raw[];
     vec2_t<T> *lds = reinterpret_cast<vec2_t<T> *>(smem_raw);
     const int Lz = g.Lz;
@@ -583,11 +584,19 @@ __global__ void __launch_bounds__(rc_max_threads<T>())
     const long s0 = (long)xcd_block(blockIdx.x, gridDim.x) * W;
     const bool live = s0 + w < Lxy;
     const vec2_t<T> *twz = tw_z<T>(g, tw), *twt = tw_t<T>(g, tw);
-    vec2_t<T> *p = D + (long)blockIdx.y * g.S + (long)z * Lxy + s0 + w;
+    // A padding column of a ragged tile reads the last site (its factor is 0
+    // and nothing of it is stored): a load under a condition of its own waits
+    // for the one before.  Only FP64 columns beyond 16 keep the condition: all
+    // their loads in flight at once take 301 registers and with them the second
+    // wave of a SIMD (27^4: 38 us against 28).
+    constexpr bool AT_ONCE = sizeof(T) * NT <= 128;
+    if ((!AT_ONCE || !tiles_first(g)) && status->done) return;
+    vec2_t<T> *p = D + (long)blockIdx.y * g.S + (long)z * Lxy + (AT_ONCE && !live ? Lxy - 1 : s0 + w);
     const long tstride = (long)Lz * Lxy;
     cpx<T> a[NT];
 #pragma unroll
-    for (int t = 0; t < NT; ++t) a[t] = live ? ld<T>(p + t * tstride) : mk<T>(0, 0);
+    for (int t = 0; t < NT; ++t) a[t] = AT_ONCE || live ? ld<T>(p + t * tstride) : mk<T>(0, 0);
+    if (AT_ONCE && status->done) return discard(a);
     const int PJ = Lz * W + ZT_PAD;
     auto base = [W, PJ](int c) { return (c / W) * PJ + (c % W); };  // c = w + W*j
     if (MODE <= 0) dft<NT, -1>(a, twt);
@@ -906,6 +915,9 @@ template <class T> fft_plan plan_fft(const geom &g, size_t zt_lds_budget, int nc
         int W = 128 / (int)e;
         while (W > 1 && (W * g.Lz > rc_max_threads<T>() || W > Lxy || rc_bytes(W) > zt_lds_budget))
             W >>= 1;
+        // lattices that would leave compute units without a block: narrower
+        // tiles, down to one wave each (their rows come from L2 anyway)
+        while (W > 1 && W * g.Lz > 64 && (Lxy + W - 1) / W * g.nf < ncu) W >>= 1;
         if (W * g.Lz <= rc_max_threads<T>() && rc_bytes(W) <= 160 * 1024) {
             p.rc = true;
             p.W = W;
@@ -931,10 +943,10 @@ inline dim3 tile2_grid(const tile2_plan &a, int nf) {
 template <class T, int MODE>
 hipError_t launch_tile2(const geom &g, vec2_t<T> *D, const vec2_t<T> *tw, const T *ptab,
                         T p2max_over_V, const tile2_plan &a, const dev_status *status,
-                        hipStream_t st) {
+                        hipStream_t st, const fold_args &fold = {}) {
     const dim3 grid = tile2_grid(a, g.nf);
 #define LGF_T2(R, N)                                                                               \
-    k_fft_tile2<T, MODE, R, N><<<grid, N, a.lds, st>>>(g, D, tw, ptab, p2max_over_V, a, status)
+    k_fft_tile2<T, MODE, R, N><<<grid, N, a.lds, st>>>(g, D, tw, ptab, p2max_over_V, a, status, fold)
     if (a.rmax > 16) LGF_T2(32, 256);
     else if (a.nthr == 1024) LGF_T2(16, 1024);
     else LGF_T2(16, 512);
@@ -1034,12 +1046,13 @@ hipError_t launch_axis(const geom &g, vec2_t<T> *D, const vec2_t<T> *twa, const 
 
 template <class T>
 hipError_t launch_fft_xy(const geom &g, void *D, int dir, const void *tw, const fft_plan &pl,
-                         const dev_status *status, hipStream_t st) {
+                         const dev_status *status, hipStream_t st, const fold_args &fold) {
+    if (fold.fp.enabled && (dir > 0 || !fft_xy_folds(pl))) return hipErrorInvalidValue;
     auto Dp = static_cast<vec2_t<T> *>(D);
     auto twp = static_cast<const vec2_t<T> *>(tw);
     if (pl.t2) {
         // (x,t) planes: forward first, inverse last
-        if (dir < 0) return launch_tile2<T, -1>(g, Dp, twp, nullptr, T(0), pl.t2a, status, st);
+        if (dir < 0) return launch_tile2<T, -1>(g, Dp, twp, nullptr, T(0), pl.t2a, status, st, fold);
         return launch_tile2<T, 1>(g, Dp, twp, nullptr, T(0), pl.t2a, status, st);
     }
     if constexpr (std::is_same<T, double>::value) {
@@ -1060,8 +1073,8 @@ hipError_t launch_fft_xy(const geom &g, void *D, int dir, const void *tw, const 
         const size_t lds = pl.lds_xy;
 #define LGF_XY(NN)                                                                            \
     case NN:                                                                                  \
-        if (dir < 0) k_fft_xy_rc<T, NN, -1><<<grid, nt, lds, st>>>(g, Dp, twp, F, status);   \
-        else k_fft_xy_rc<T, NN, 1><<<grid, nt, lds, st>>>(g, Dp, twp, F, status);            \
+        if (dir < 0) k_fft_xy_rc<T, NN, -1><<<grid, nt, lds, st>>>(g, Dp, twp, F, status, fold);   \
+        else k_fft_xy_rc<T, NN, 1><<<grid, nt, lds, st>>>(g, Dp, twp, F, status, fold);            \
         break;
         switch (g.Ly) {
             LGF_FFT_SMALL_EXTENTS(LGF_XY)
@@ -1084,11 +1097,11 @@ hipError_t launch_fft_xy(const geom &g, void *D, int dir, const void *tw, const 
     }
     dim3 grid((unsigned)(g.Lz * g.Lt), (unsigned)g.nf);
     if (fft_tier(g.Lx) <= 16 && fft_tier(g.Ly) <= 16) {
-        if (dir < 0) k_fft_xy<T, -1, 16><<<grid, XY_BLOCK, pl.lds_xy, st>>>(g, Dp, twp, status);
-        else k_fft_xy<T, +1, 16><<<grid, XY_BLOCK, pl.lds_xy, st>>>(g, Dp, twp, status);
+        if (dir < 0) k_fft_xy<T, -1, 16><<<grid, XY_BLOCK, pl.lds_xy, st>>>(g, Dp, twp, status, fold);
+        else k_fft_xy<T, +1, 16><<<grid, XY_BLOCK, pl.lds_xy, st>>>(g, Dp, twp, status, fold);
     } else {
-        if (dir < 0) k_fft_xy<T, -1, 32><<<grid, XY_BLOCK, pl.lds_xy, st>>>(g, Dp, twp, status);
-        else k_fft_xy<T, +1, 32><<<grid, XY_BLOCK, pl.lds_xy, st>>>(g, Dp, twp, status);
+        if (dir < 0) k_fft_xy<T, -1, 32><<<grid, XY_BLOCK, pl.lds_xy, st>>>(g, Dp, twp, status, fold);
+        else k_fft_xy<T, +1, 32><<<grid, XY_BLOCK, pl.lds_xy, st>>>(g, Dp, twp, status, fold);
     }
     return hipGetLastError();
 }

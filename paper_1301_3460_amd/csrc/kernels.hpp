@@ -38,6 +38,7 @@ struct fin_params {
     int max_iter, increment, hist_cap, enabled;
     int stall;  // > 0: stop with ST_STALLED after this many sweeps without a new minimum
     double *histF, *histT;
+    dev_status *host = nullptr;  // pinned copy of the state for the host (finalize kernel)
 };
 
 // Component arrays of links and Fourier fields are S = V + SOA_PAD elements
@@ -135,6 +136,16 @@ hipError_t launch_update(const geom &g, const void *Lin, void *Lout, const void 
 hipError_t launch_update_u0(const geom &g, const void *U0, const void *G, void *Dout,
                             double *partials, dev_status *status, const fin_params &fp,
                             hipStream_t st);
+// The update of FP64 sweeps of small lattices that store their links
+// (UPDATE_DIRS_MAX_SITES, 12 reals, SU(3)): launch_update<double> with a lane
+// per link, update_dirs_parts pairs of partials.
+// 8^4 9.7 -> 5.9 us, 16 x 8^3 10.5 -> 6.7, 64 x 6 x 6 x 4 11.5 -> 8; it forms
+// every g eight times, and at 12 x 16 x 12 x 8 (18432 sites) the gain is gone.
+constexpr long UPDATE_DIRS_MAX_SITES = 20480;
+int update_dirs_parts(const geom &g);
+hipError_t launch_update_dirs(const geom &g, const void *Lin, void *Lout, const void *LD,
+                              void *Dout, double c, bool exact, void *GX, double *partials,
+                              dev_status *status, const fin_params &fp, hipStream_t st);
 // Caller links U_mu(x) = G(x) U0_mu(x) G(x+mu)^dagger from U0 (SoA, 12 reals)
 hipError_t launch_unpack_rotated(const void *U0, const void *G, double *Uaos, const geom &g,
                                  hipStream_t st);
@@ -205,10 +216,46 @@ template <class T> void fft_set_max_lds(const geom &g, const fft_plan &p);
 void update_set_max_lds();
 // Twiddle tables: one buffer per real type with the axis tables
 // exp(-2 pi i j / L_mu), j < L_mu, of x, y, z and t one after the other.
-// (x,y) transform, dir -1 forward, +1 inverse
+// The stopping test of the sweep before, taken along by the first kernel of
+// the next one (fp.enabled): the state goes from the kernel's status pointer
+// to `out`, another slot, which the kernels after it read.
+struct fold_args {
+    const double *partials = nullptr;
+    int nparts = 0;
+    dev_status *out = nullptr;
+    fin_params fp{};
+};
+// (x,y) transform, dir -1 forward, +1 inverse; fold: forward only, where
+// fft_xy_folds
 template <class T>
 hipError_t launch_fft_xy(const geom &g, void *D, int dir, const void *tw, const fft_plan &pl,
-                         const dev_status *status, hipStream_t st);
+                         const dev_status *status, hipStream_t st, const fold_args &fold = {});
+bool fft_xy_folds(const fft_plan &pl);
+// pairs of partials up to which it rides along and the test's own kernel is one
+// wave: each wave then reads at most ten pairs per lane (8^4: 27 against 23 us
+// per sweep with the tile loads under the state's latency; the kernel of its
+// own took 3.1 us there and 4.0 at 16^4)
+constexpr int FOLD_MAX_PARTS = 640;
+// Small lattices: the whole transform of a field in one block (fft_small.hip)
+struct small_plan {
+    bool on = false;
+    int order[4] = {0, 1, 2, 3};  // axes of the forward transform; the last one scales
+    int rmax = 16;                // register tier of the largest extent
+    size_t lds = 0;
+};
+// One block per field: its four compute units carry the whole transform, so it
+// pays where launches cost more than arithmetic.  Per sweep against the general
+// passes: 4^4 25.8 -> 20.6 us, 9 x 4 x 6 x 8 30 -> 23, but 8^4 24.6 -> 26.7 and
+// 16 x 8^3 26.4 -> 34.7.
+constexpr long SMALL_MAX_SITES = 2048;
+constexpr size_t SMALL_LDS_MAX = 144 * 1024;
+template <class T> small_plan plan_small(const geom &g, const fft_plan &p);
+template <class T> void small_set_max_lds(const small_plan &s);
+// The round trip of all fields and the stopping test `fold` of the sweep before
+template <class T>
+hipError_t launch_fft4_small(const geom &g, void *D, const void *tw, const T *ptab, T p2max_over_V,
+                             const small_plan &sp, const dev_status *status, const fold_args &fold,
+                             hipStream_t st);
 // Inverse (x,y) pass on the field of real type T fused with G(x) <- g(x) G(x),
 // G of real type TG (SU(3) sweeps that keep U0 and G; L Delta itself is not
 // stored), when xy_acc_fusable: register-column planes with all 4 fields in

@@ -522,6 +522,30 @@ LGF_HD T delta_pack(const xacc<T> &a, cpx<T> &f0, cpx<T> &f1, cpx<T> &f2, cpx<T>
     return T(2) * (norm2(f0) + norm2(f1) + norm2(f2)) + da * da + db * db + (da + db) * (da + db);
 }
 
+// The divergence is linear in the links through P(M): the off-diagonal
+// differences M_ij - conj(M_ji) (i < j) and the traceless part of 2 Im M_ii, 8
+// reals, in the order of the 4 Fourier-field entries.
+// a += sgn * P(m)
+template <class T> LGF_HD void proj_add(T (&a)[8], const mat3<T> &m, T sgn) {
+    a[0] += sgn * (m.e[0][1].re - m.e[1][0].re);
+    a[1] += sgn * (m.e[0][1].im + m.e[1][0].im);
+    a[2] += sgn * (m.e[0][2].re - m.e[2][0].re);
+    a[3] += sgn * (m.e[0][2].im + m.e[2][0].im);
+    a[4] += sgn * (m.e[1][2].re - m.e[2][1].re);
+    a[5] += sgn * (m.e[1][2].im + m.e[2][1].im);
+    const T d0 = T(2) * m.e[0][0].im, d1 = T(2) * m.e[1][1].im, d2 = T(2) * m.e[2][2].im;
+    const T tr = (d0 + d1 + d2) * T(1.0 / 3.0);
+    a[6] += sgn * (d0 - tr);
+    a[7] += sgn * (d1 - tr);
+}
+
+// P(m) alone
+template <class T> LGF_HD void proj_of(T (&a)[8], const mat3<T> &m) {
+#pragma unroll
+    for (int k = 0; k < 8; ++k) a[k] = T(0);
+    proj_add(a, m, T(1));
+}
+
 template <class T> LGF_HD T retrace(const mat3<T> &m) {
     return m.e[0][0].re + m.e[1][1].re + m.e[2][2].re;
 }

@@ -110,85 +110,6 @@ __global__ void k_matrix_from_field(const double2 *__restrict__ D, double2 *__re
 
 constexpr int FIN_BLOCK = 1024;
 
-template <int NT>
-__device__ __forceinline__ void fixed_order_sum(const double *__restrict__ partials, int nparts,
-                                                double &A, double &B) {
-    // thread t adds pairs t, t + NT, t + 2 NT, ... in that order; four 16-byte
-    // loads are in flight per step
-    const double2 *p2 = reinterpret_cast<const double2 *>(partials);
-    double a = 0, b = 0;
-    int i = threadIdx.x;
-    for (; i + 3 * NT < nparts; i += 4 * NT) {
-        const double2 v0 = p2[i], v1 = p2[i + NT], v2 = p2[i + 2 * NT], v3 = p2[i + 3 * NT];
-        a += v0.x;
-        b += v0.y;
-        a += v1.x;
-        b += v1.y;
-        a += v2.x;
-        b += v2.y;
-        a += v3.x;
-        b += v3.y;
-    }
-    for (; i < nparts; i += NT) {
-        const double2 v = p2[i];
-        a += v.x;
-        b += v.y;
-    }
-    __shared__ double sa[NT], sb[NT];
-    sa[threadIdx.x] = a;
-    sb[threadIdx.x] = b;
-    __syncthreads();
-    for (int h = NT / 2; h > 0; h >>= 1) {
-        if (threadIdx.x < h) {
-            sa[threadIdx.x] += sa[threadIdx.x + h];
-            sb[threadIdx.x] += sb[threadIdx.x + h];
-        }
-        __syncthreads();
-    }
-    A = sa[0];
-    B = sb[0];
-}
-
-// F = A normF, theta = B normT; history, stopping test (one thread)
-__device__ __forceinline__ void finalize_state(double A, double B, dev_status *status,
-                                               const fin_params &fp) {
-    const double F = A * fp.normF, th = B * fp.normT;
-    dev_status st = *status;
-    if (fp.increment) st.n += 1;
-    const int h = st.hist_base + st.n;
-    if (h < fp.hist_cap) {
-        fp.histF[h] = F;
-        fp.histT[h] = th;
-    }
-    st.F = F;
-    st.theta = th;
-    if (!isfinite(th) || !isfinite(F)) {
-        st.done = 1;
-        st.code = ST_NONFINITE;
-    } else if (th < fp.tol) {
-        st.done = 1;
-        st.code = ST_CONVERGED;
-    } else if (st.n >= fp.max_iter) {
-        st.done = 1;
-        st.code = ST_MAXITER;
-    } else if (fp.tol > 0) {
-        // a solve (tol > 0) also stops when theta diverges or stalls; a fixed
-        // count of sweeps (tol == 0) runs them all
-        st.rises = (st.n > 0 && th > st.theta_prev) ? st.rises + 1 : 0;
-        st.since_min = (st.n == 0 || th < st.theta_min) ? 0 : st.since_min + 1;
-        if (st.rises >= DIVERGE_RISES && th > DIVERGE_GROWTH * st.theta_min) {
-            st.done = 1;
-            st.code = ST_DIVERGING;
-        } else if (fp.stall > 0 && st.since_min >= fp.stall) {
-            st.done = 1;
-            st.code = ST_STALLED;
-        }
-    }
-    st.theta_prev = th;
-    st.theta_min = (st.n == 0 || th < st.theta_min) ? th : st.theta_min;
-    *status = st;
-}
-
 // ---------------------------------------------------------------------------
 // divergence and reductions of given links (first sweep of a solve)
 // ---------------------------------------------------------------------------
@@ -327,6 +248,112 @@ __global__ void __launch_bounds__(SITE_BLOCK)
         st_stream<TF>(Dout + 3 * g.S + s, cvt<TF>(f3));
     }
     block_sum2<SITE_BLOCK>(fs, ts, partials, blockIdx.x);
+}
+
+// ---------------------------------------------------------------------------
+// the update of small lattices: a lane per half-step
+// ---------------------------------------------------------------------------
+
+// A small lattice's update is bound by the latency of one thread's chain of
+// eight half-steps (and by fetching the unrolled code for them), not by memory
+// or arithmetic: 9.7 us at 8^4.  Here the eight lanes of a site each form one
+// link, so that all loads go out at once; a site's g is formed by all eight.
+// FP64 links of 12 reals; GPRE as in k_update.  5.9 us at 8^4.
+constexpr int DIR_SITES = SITE_BLOCK / 8;
+inline int dir_blocks(long V) { return (int)((V + DIR_SITES - 1) / DIR_SITES); }
+
+template <class TF, bool GPRE>
+__global__ void __launch_bounds__(SITE_BLOCK)
+    k_update_dirs(geom g, const double2 *__restrict__ Lin, double2 *__restrict__ Lout,
+                  const vec2_t<TF> *__restrict__ LD, const double2 *__restrict__ GX,
+                  vec2_t<TF> *__restrict__ Dout, double c, double *__restrict__ partials,
+                  const dev_status *__restrict__ status) {
+    using T = double;
+    const long s0 = (long)xcd_block(blockIdx.x, gridDim.x) * DIR_SITES + (threadIdx.x >> 3);
+    const bool live = s0 < g.V;
+    const long s = live ? s0 : g.V - 1;
+    const int h = threadIdx.x & 7, mu = h >> 1;
+    const bool in = h & 1;  // the link arriving from x - mu
+    const nbr n = neighbours(g, s);
+    const long sp = mu == 0 ? n.p[0] : mu == 1 ? n.p[1] : mu == 2 ? n.p[2] : n.p[3];
+    const long sm = mu == 0 ? n.m[0] : mu == 1 ? n.m[1] : mu == 2 ? n.m[2] : n.m[3];
+    const long q = in ? sm : sp;  // the other end of the link
+    constexpr int NG = GPRE ? 6 : 4;
+    cpx<T> fo[NG], fq[NG], u[6];
+    auto load_g = [&](long x, cpx<T> (&f)[NG]) {
+#pragma unroll
+        for (int k = 0; k < NG; ++k) {
+            if constexpr (GPRE) f[k] = ld<T>(GX + (long)k * g.S + x);
+            else f[k] = cvt<T>(ld<TF>(LD + (long)k * g.S + x));
+        }
+    };
+    load_g(s, fo);
+    load_g(q, fq);
+    const double2 *lp = Lin + (long)mu * 6 * g.S + (in ? sm : s);
+#pragma unroll
+    for (int k = 0; k < 6; ++k) u[k] = ld<T>(lp + (long)k * g.S);
+    if (status->done) {
+        discard(fo);
+        discard(fq);
+        return discard(u);
+    }
+    // the link's ends in its own order: left at its site, right at the next
+    cpx<T> fl[NG], fr[NG];
+#pragma unroll
+    for (int k = 0; k < NG; ++k) {
+        fl[k] = in ? fq[k] : fo[k];
+        fr[k] = in ? fo[k] : fq[k];
+    }
+    auto make_g = [&](const cpx<T> (&f)[NG]) {
+        mat3<T> m;
+        if constexpr (GPRE) {
+#pragma unroll
+            for (int k = 0; k < 6; ++k) m.e[k / 3][k % 3] = f[k];
+            rebuild_row2(m);
+        } else {
+            m = gauge_from_entries<T>(f[0], f[1], f[2], f[3], c);
+        }
+        return m;
+    };
+    const mat3<T> un = mul_abcd<2>(make_g(fl), link_from_slots<T, 12>(u), make_g(fr));
+    if (live && !in) store_link<T, 12>(Lout, g.S, mu, s, un);
+    // The sixteen reals a link adds to the divergence and to F go through LDS,
+    // so that each is summed over the half-steps in the order of k_update and
+    // k_div_reduce: lane h sums reals 2h and 2h + 1.
+    __shared__ T X[DIR_SITES][16][9];
+    T(*mine)[9] = X[threadIdx.x >> 3];
+    const T sg = in ? T(1) : T(-1);
+    auto put = [&](int k, cpx<T> m) {
+        mine[2 * k][h] = sg * m.re;
+        mine[2 * k + 1][h] = sg * m.im;
+    };
+    put(0, un.e[0][1]);
+    put(1, un.e[1][0]);
+    put(2, un.e[0][2]);
+    put(3, un.e[2][0]);
+    put(4, un.e[1][2]);
+    put(5, un.e[2][1]);
+    mine[12][h] = sg * un.e[0][0].im;
+    mine[13][h] = sg * un.e[1][1].im;
+    mine[14][h] = sg * un.e[2][2].im;
+    mine[15][h] = in ? T(0) : retrace(un);
+    __syncthreads();
+    cpx<T> x = mk<T>(0, 0);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) x = x + mk<T>(mine[2 * h][k], mine[2 * h + 1][k]);
+    // lanes 2k, 2k + 1 hold the two entries of field k (lane 6 Im of the first
+    // two diagonal entries, lane 7 Im of the third and the trace)
+    const cpx<T> o = mk<T>(__shfl_xor(x.re, 1), __shfl_xor(x.im, 1));
+    const T d0 = T(2) * x.re, d1 = T(2) * x.im, d2 = T(2) * o.re;
+    const T t3 = (d0 + d1 + d2) * T(1.0 / 3.0);
+    const cpx<T> f = h == 6 ? mk<T>(d0 - t3, d1 - t3) : x - conjg(o);
+    if (live && (h & 1) == 0) st<TF>(Dout + (long)(h >> 1) * g.S + s, cvt<TF>(f));
+    // Tr[Delta Delta^dagger], once per site
+    T th = h == 6 ? f.re * f.re + f.im * f.im + (f.re + f.im) * (f.re + f.im) : T(2) * norm2(f);
+    th += __shfl_xor(th, 2);
+    th += __shfl_xor(th, 4);
+    block_sum2<SITE_BLOCK>(live && h == 7 ? x.im : 0.0, live && h == 0 ? th : 0.0, partials,
+                           blockIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -513,33 +540,14 @@ __global__ void __launch_bounds__(SITE_BLOCK)
 // share a compute unit, so that one block's loads overlap the other's
 // arithmetic: 73 against 82 us at 32^4 and 797 against 828 us at 48^3 x 96
 // for one block of 256 x 4 (or 256 x 2: 74 / 848 us; 128 x 2: 73 / 855 us).
-constexpr int UPDS_XY = 128, UPDS_T = 4, UPDS_THREADS = UPDS_XY * UPDS_T;
-constexpr size_t UPDS_LDS = (size_t)8 * 4 * UPDS_THREADS * sizeof(float);
+// Lattices with less than one such block per compute unit take blocks of 64 x 4.
+constexpr int UPDS_T = 4;
+constexpr long UPDS_SPLIT_SITES = 131072;
+template <int XY> constexpr size_t upds_lds() { return (size_t)8 * 4 * XY * UPDS_T * sizeof(float); }
 
 inline bool update_shared_ok(const geom &g) {
     const long Lxy = (long)g.Lx * g.Ly;
-    return g.nc == 3 && g.lf == 12 && Lxy % UPDS_XY == 0 && g.Lt % UPDS_T == 0;
-}
-
-// a += sgn * P(m)
-template <class T> LGF_HD void proj_add(T (&a)[8], const mat3<T> &m, T sgn) {
-    a[0] += sgn * (m.e[0][1].re - m.e[1][0].re);
-    a[1] += sgn * (m.e[0][1].im + m.e[1][0].im);
-    a[2] += sgn * (m.e[0][2].re - m.e[2][0].re);
-    a[3] += sgn * (m.e[0][2].im + m.e[2][0].im);
-    a[4] += sgn * (m.e[1][2].re - m.e[2][1].re);
-    a[5] += sgn * (m.e[1][2].im + m.e[2][1].im);
-    const T d0 = T(2) * m.e[0][0].im, d1 = T(2) * m.e[1][1].im, d2 = T(2) * m.e[2][2].im;
-    const T tr = (d0 + d1 + d2) * T(1.0 / 3.0);
-    a[6] += sgn * (d0 - tr);
-    a[7] += sgn * (d1 - tr);
-}
-
-// P(m) alone
-template <class T> LGF_HD void proj_of(T (&a)[8], const mat3<T> &m) {
-#pragma unroll
-    for (int k = 0; k < 8; ++k) a[k] = T(0);
-    proj_add(a, m, T(1));
+    return g.nc == 3 && g.lf == 12 && Lxy % 128 == 0 && g.Lt % UPDS_T == 0;
 }
 
 // block sum of two doubles per group of NG threads into partials[2 * (slot0 + group) + {0,1}]
@@ -573,11 +581,13 @@ __device__ __forceinline__ void group_sum2(double a, double b, double *partials,
 }
 
 // four waves per SIMD: two blocks per compute unit (at most 128 VGPRs)
-__global__ void __launch_bounds__(UPDS_THREADS) __attribute__((amdgpu_waves_per_eu(4)))
+template <int UPDS_XY>
+__global__ void __launch_bounds__(UPDS_XY * UPDS_T) __attribute__((amdgpu_waves_per_eu(4)))
     k_update_shared32(geom g, const float2 *__restrict__ Lin, const float2 *__restrict__ GX,
                       float2 *__restrict__ Dout, double *__restrict__ partials,
                       const dev_status *__restrict__ status) {
     using T = float;
+    constexpr int UPDS_THREADS = UPDS_XY * UPDS_T;
     if (status->done) return;
     extern __shared__ unsigned char smem_raw[];
     T *P = reinterpret_cast<T *>(smem_raw);  // P[(k * 4 + mu) * UPDS_THREADS + i]
@@ -692,8 +702,8 @@ __global__ void __launch_bounds__(UPDS_THREADS) __attribute__((amdgpu_waves_per_
 }
 
 void update_set_max_lds() {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_update_shared32),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)UPDS_LDS);
+    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_update_shared32<128>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)upds_lds<128>());
 }
 
 // reorder 4 fields between natural index order and transform-position order
@@ -719,10 +729,20 @@ __global__ void k_reorder(geom g, const double2 *__restrict__ in, long si, doubl
 __global__ void __launch_bounds__(FIN_BLOCK)
     k_finalize(const double *__restrict__ partials, int nparts, dev_status *__restrict__ status,
                fin_params fp) {
-    if (status->done) return;
-    double A, B;
-    fixed_order_sum<FIN_BLOCK>(partials, nparts, A, B);
-    if (threadIdx.x == 0) finalize_state(A, B, status, fp);
+    dev_status st = *status;
+    if (!st.done) {
+        double A, B;
+        if (nparts <= FOLD_MAX_PARTS) wave_sum(partials, nparts, A, B);  // launched with one wave
+        else fixed_order_sum<FIN_BLOCK>(partials, nparts, A, B);
+        st = next_state(A, B, st, fp, threadIdx.x == 0);
+        if (threadIdx.x == 0) *status = st;
+    }
+    // straight into pinned host memory: a copy of its own would be another
+    // launch per batch of sweeps
+    if (threadIdx.x == 0 && fp.host) {
+        *fp.host = st;
+        __threadfence_system();
+    }
 }
 
 __global__ void k_status_reset(dev_status *status, int hist_base) {
@@ -847,6 +867,11 @@ __global__ void __launch_bounds__(SITE_BLOCK)
 
 static inline unsigned nblk(long n, int b) { return (unsigned)((n + b - 1) / b); }
 
+static void finalize(const double *partials, int nparts, dev_status *status, const fin_params &fp,
+                     hipStream_t st) {
+    k_finalize<<<1, nparts <= FOLD_MAX_PARTS ? 64 : FIN_BLOCK, 0, st>>>(partials, nparts, status, fp);
+}
+
 template <class T>
 hipError_t launch_pack_links(const double *Uaos, void *L, const geom &g, hipStream_t st) {
     if (g.nc == 2) return launch_pack_su2<T>(Uaos, L, g, st);
@@ -935,7 +960,7 @@ hipError_t launch_div_reduce(const geom &g, const void *L, void *D, double *part
         return hipGetLastError();
     });
     if (e != hipSuccess) return e;
-    if (fp.enabled) k_finalize<<<1, FIN_BLOCK, 0, st>>>(partials, site_blocks(g.V), status, fp);
+    if (fp.enabled) finalize(partials, site_blocks(g.V), status, fp, st);
     return hipGetLastError();
 }
 template hipError_t launch_div_reduce<double>(const geom &, const void *, void *, double *,
@@ -972,9 +997,15 @@ hipError_t launch_update(const geom &g, const void *Lin, void *Lout, const void 
         if constexpr (ACC) {
             // links G U0 G^dagger from the constant copy U0 (Lin), not stored
             if (update_shared_ok(g)) {
-                k_update_shared32<<<(unsigned)(g.V / UPDS_THREADS), UPDS_THREADS, UPDS_LDS, st>>>(
-                    g, static_cast<const float2 *>(Lin), static_cast<const float2 *>(GX),
-                    static_cast<float2 *>(Dout), partials, status);
+                auto shared = [&](auto xy) {
+                    constexpr int XY = decltype(xy)::value;
+                    k_update_shared32<XY>
+                        <<<(unsigned)(g.V / (XY * UPDS_T)), XY * UPDS_T, upds_lds<XY>(), st>>>(
+                            g, static_cast<const float2 *>(Lin), static_cast<const float2 *>(GX),
+                            static_cast<float2 *>(Dout), partials, status);
+                };
+                if (g.V < UPDS_SPLIT_SITES) shared(std::integral_constant<int, 64>{});
+                else shared(std::integral_constant<int, 128>{});
                 return hipGetLastError();
             }
             if (g.lf == 18) go(k_update<T, TF, true, 18, false>);
@@ -993,7 +1024,7 @@ hipError_t launch_update(const geom &g, const void *Lin, void *Lout, const void 
         return hipGetLastError();
     });
     if (e != hipSuccess) return e;
-    if (fp.enabled) k_finalize<<<1, FIN_BLOCK, 0, st>>>(partials, site_blocks(g.V), status, fp);
+    if (fp.enabled) finalize(partials, site_blocks(g.V), status, fp, st);
     return hipGetLastError();
 }
 template <class TF, class TG>
@@ -1018,6 +1049,36 @@ template hipError_t launch_gauge_acc<double, double>(const geom &, const void *,
                                                      void *, double, bool, const dev_status *,
                                                      hipStream_t);
 
+int update_dirs_parts(const geom &g) { return dir_blocks(g.V); }
+
+hipError_t launch_update_dirs(const geom &g, const void *Lin, void *Lout, const void *LD,
+                              void *Dout, double c, bool exact, void *GX, double *partials,
+                              dev_status *status, const fin_params &fp, hipStream_t st) {
+    if (g.nc != 3 || g.lf != 12) return hipErrorInvalidValue;
+    const int nb = dir_blocks(g.V);
+    auto Li = static_cast<const double2 *>(Lin);
+    auto Lo = static_cast<double2 *>(Lout);
+    auto G = static_cast<double2 *>(GX);
+    auto go = [&](auto tf) {
+        using TF = decltype(tf);
+        auto LDp = static_cast<const vec2_t<TF> *>(LD);
+        auto Dp = static_cast<vec2_t<TF> *>(Dout);
+        if (exact) {
+            k_gauge_exp<double, TF><<<nblk(g.V, 256), 256, 0, st>>>(g, LDp, G, c, status);
+            k_update_dirs<TF, true><<<nb, SITE_BLOCK, 0, st>>>(g, Li, Lo, LDp, G, Dp, c, partials, status);
+        } else {
+            k_update_dirs<TF, false><<<nb, SITE_BLOCK, 0, st>>>(g, Li, Lo, LDp, G, Dp, c, partials, status);
+        }
+    };
+    if (exact && !GX) return hipErrorInvalidValue;
+    if (g.ff32) go(float{});
+    else go(double{});
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || !fp.enabled) return e;
+    finalize(partials, nb, status, fp, st);
+    return hipGetLastError();
+}
+
 hipError_t launch_update_u0(const geom &g, const void *U0, const void *G, void *Dout,
                             double *partials, dev_status *status, const fin_params &fp,
                             hipStream_t st) {
@@ -1031,7 +1092,7 @@ hipError_t launch_update_u0(const geom &g, const void *U0, const void *G, void *
     else go(k_update_u0<double>, static_cast<double2 *>(Dout));
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (fp.enabled) k_finalize<<<1, FIN_BLOCK, 0, st>>>(partials, site_blocks(g.V), status, fp);
+    if (fp.enabled) finalize(partials, site_blocks(g.V), status, fp, st);
     return hipGetLastError();
 }
 
@@ -1059,7 +1120,7 @@ hipError_t launch_reorder_fields(const geom &g, const double2 *in, long si, doub
 
 hipError_t launch_finalize(const double *partials, int nparts, dev_status *status,
                            const fin_params &fp, hipStream_t st) {
-    k_finalize<<<1, FIN_BLOCK, 0, st>>>(partials, nparts, status, fp);
+    finalize(partials, nparts, status, fp, st);
     return hipGetLastError();
 }
 
@@ -1116,7 +1177,7 @@ hipError_t launch_switch_div(const geom &g, const void *G32, const double *U0aos
         return hipGetLastError();
     });
     if (e != hipSuccess) return e;
-    if (fp.enabled) k_finalize<<<1, FIN_BLOCK, 0, st>>>(partials, site_blocks(g.V), status, fp);
+    if (fp.enabled) finalize(partials, site_blocks(g.V), status, fp, st);
     return hipGetLastError();
 }
 
