@@ -72,6 +72,14 @@ template <class T> LGF_HD void st_stream(vec2_t<T> *p, cpx<T> a) {
     __builtin_nontemporal_store(v, reinterpret_cast<v2 *>(p));
 }
 
+// Streaming load: marked non-temporal, so that data a sweep reads once does not
+// push what the next kernels read out of the last-level cache.
+template <class T> LGF_HD cpx<T> ld_stream(const vec2_t<T> *p) {
+    typedef T v2 __attribute__((ext_vector_type(2)));
+    const v2 v = __builtin_nontemporal_load(reinterpret_cast<const v2 *>(p));
+    return {v.x, v.y};
+}
+
 // 3x3 complex matrix, row-major.
 template <class T> struct mat3 {
     cpx<T> e[3][3];

@@ -519,7 +519,7 @@ __global__ void __launch_bounds__(SITE_BLOCK)
 }
 
 // ---------------------------------------------------------------------------
-// FP32 sweeps of an SU(3) mixed solve with the links shared through LDS
+// sweeps that keep U0 and G with the links shared through LDS
 // ---------------------------------------------------------------------------
 
 // Every link U_mu(x) enters two divergences: with sign - at x and with sign +
@@ -532,7 +532,7 @@ __global__ void __launch_bounds__(SITE_BLOCK)
 // UPDS_XY consecutive xy-sites at UPDS_T consecutive t and one z: the x
 // neighbour is in the block whenever UPDS_XY is a multiple of Lx, the y
 // neighbour except in the block's first xy-row, the t neighbour except at
-// its first t, the z neighbour never.  FP32 arithmetic as in k_update; the
+// its first t, the z neighbour never.  Arithmetic as in k_update; the
 // per-link projections change the rounding order of the sums, not the
 // quantities.  Partial sums go out per group of SITE_BLOCK threads, so the
 // finalize reads the same number of partials as after k_update.
@@ -543,7 +543,25 @@ __global__ void __launch_bounds__(SITE_BLOCK)
 // Lattices with less than one such block per compute unit take blocks of 64 x 4.
 constexpr int UPDS_T = 4;
 constexpr long UPDS_SPLIT_SITES = 131072;
-template <int XY> constexpr size_t upds_lds() { return (size_t)8 * 4 * XY * UPDS_T * sizeof(float); }
+template <class T, int XY> constexpr size_t upds_lds() { return (size_t)8 * 3 * XY * UPDS_T * sizeof(T); }
+
+// FP32: the loads of U0's x, y and t links (each read once by its own block)
+// are streaming where the sweep's data do not fit the 256 MB last-level cache
+// but all besides U0 (G twice, the field twice: 160 bytes per site) do: what
+// the next kernels read then stays there (32^4: sweep 154 -> 147 us, the
+// transforms 73 -> 68; 48^3 x 96, where nothing fits, 1681 -> 1715).
+inline bool upds_stream(const geom &g) {
+    const double mall = 256.0 * 1024 * 1024;
+    return 368.0 * g.V > mall && 160.0 * g.V < mall;
+}
+
+// FP64 (sweeps that keep U0 and G): blocks of 64 x 4, two per compute unit, two
+// waves per SIMD, where k_update_u0's neighbour reads leave L2: 32^4 147 -> 136
+// us, 24^3 x 48 98 -> 94, 48^3 x 96 1531 -> 1512, but 16^2 x 32^2 32.1 -> 34.3
+// and 24^4 43.9 -> 47.6.  Streaming loads do not help here (136 -> 140).
+inline bool update_shared64_ok(const geom &g) {
+    return g.keeps_u0() && g.V >= 524288 && (long)g.Lx * g.Ly % 64 == 0 && g.Lt % UPDS_T == 0;
+}
 
 inline bool update_shared_ok(const geom &g) {
     const long Lxy = (long)g.Lx * g.Ly;
@@ -580,17 +598,20 @@ __device__ __forceinline__ void group_sum2(double a, double b, double *partials,
     }
 }
 
-// four waves per SIMD: two blocks per compute unit (at most 128 VGPRs)
-template <int UPDS_XY>
-__global__ void __launch_bounds__(UPDS_XY * UPDS_T) __attribute__((amdgpu_waves_per_eu(4)))
-    k_update_shared32(geom g, const float2 *__restrict__ Lin, const float2 *__restrict__ GX,
-                      float2 *__restrict__ Dout, double *__restrict__ partials,
-                      const dev_status *__restrict__ status) {
-    using T = float;
+// FP32: four waves per SIMD, two blocks per compute unit (at most 128 VGPRs);
+// FP64: two and 256
+__device__ constexpr int mu_slot(int mu) { return mu == 3 ? 2 : mu; }
+
+template <class T, class TF, int UPDS_XY, bool STREAM>
+__global__ void __launch_bounds__(UPDS_XY * UPDS_T)
+    __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2)))
+    k_update_shared(geom g, const vec2_t<T> *__restrict__ Lin, const vec2_t<T> *__restrict__ GX,
+                    vec2_t<TF> *__restrict__ Dout, double *__restrict__ partials,
+                    const dev_status *__restrict__ status) {
     constexpr int UPDS_THREADS = UPDS_XY * UPDS_T;
     if (status->done) return;
     extern __shared__ unsigned char smem_raw[];
-    T *P = reinterpret_cast<T *>(smem_raw);  // P[(k * 4 + mu) * UPDS_THREADS + i]
+    T *P = reinterpret_cast<T *>(smem_raw);  // P[(k * 3 + mu_slot) * UPDS_THREADS + i], x, y, t
     // block -> (z fastest, then the xy group, then the t group); XCDs walk
     // contiguous ranges
     const int B = xcd_block(blockIdx.x, gridDim.x);
@@ -627,14 +648,17 @@ __global__ void __launch_bounds__(UPDS_XY * UPDS_T) __attribute__((amdgpu_waves_
         cpx<T> f[6], u[6];
     };
     // h = 2 mu + b as in k_update: b = 0 the link leaving x, b = 1 the one arriving from x - mu
-    auto fetch = [&](int h, half &d) {
+    auto fetch = [&](int h, half &d, bool halo = false) {
         const int mu = h >> 1;
         const unsigned sf = nb(mu, (h & 1) == 0);
         const unsigned sl = (h & 1) ? sf : s;
         load_g(sf, d.f);
-        const float2 *lp = Lin + (long)mu * 6 * S + sl;
+        const vec2_t<T> *lp = Lin + (long)mu * 6 * S + sl;
+        // the z links are read by two blocks and come from L2 the second time
+        const bool stream = STREAM && mu != 2 && (halo || (h & 1) == 0);
 #pragma unroll
-        for (int k = 0; k < 6; ++k) d.u[k] = ld<T>(lp + (long)k * S);
+        for (int k = 0; k < 6; ++k)
+            d.u[k] = stream ? ld_stream<T>(lp + (long)k * S) : ld<T>(lp + (long)k * S);
     };
     cpx<T> own[6];
     load_g(s, own);
@@ -658,7 +682,7 @@ __global__ void __launch_bounds__(UPDS_XY * UPDS_T) __attribute__((amdgpu_waves_
         proj_of(pm, un);
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
-            P[(k * 4 + mu) * UPDS_THREADS + i] = pm[k];
+            if (mu != 2) P[(k * 3 + mu_slot(mu)) * UPDS_THREADS + i] = pm[k];
             X[k] -= pm[k];
         }
     }
@@ -681,10 +705,10 @@ __global__ void __launch_bounds__(UPDS_XY * UPDS_T) __attribute__((amdgpu_waves_
         if (lx < (unsigned)UPDS_XY && lt < (unsigned)UPDS_T) {
             const int j = (int)(lt * UPDS_XY + lx);
 #pragma unroll
-            for (int k = 0; k < 8; ++k) X[k] += P[(k * 4 + mu) * UPDS_THREADS + j];
+            for (int k = 0; k < 8; ++k) X[k] += P[(k * 3 + mu_slot(mu)) * UPDS_THREADS + j];
         } else {
             half e;
-            fetch(2 * mu + 1, e);
+            fetch(2 * mu + 1, e, true);
             const mat3<T> umn = mul_abcd<2>(make_g(e.f), link_from_slots<T, 12>(e.u), g0);
             proj_add(X, umn, T(1));
         }
@@ -693,17 +717,17 @@ __global__ void __launch_bounds__(UPDS_XY * UPDS_T) __attribute__((amdgpu_waves_
                  f3 = mk<T>(X[6], X[7]);
     const T da = X[6], db = X[7];
     const T th = T(2) * (norm2(f0) + norm2(f1) + norm2(f2)) + da * da + db * db + (da + db) * (da + db);
-    st_stream<T>(Dout + s, f0);
-    st_stream<T>(Dout + S + s, f1);
-    st_stream<T>(Dout + 2 * S + s, f2);
-    st_stream<T>(Dout + 3 * S + s, f3);
+    st_stream<TF>(Dout + s, cvt<TF>(f0));
+    st_stream<TF>(Dout + S + s, cvt<TF>(f1));
+    st_stream<TF>(Dout + 2 * S + s, cvt<TF>(f2));
+    st_stream<TF>(Dout + 3 * S + s, cvt<TF>(f3));
     group_sum2<UPDS_THREADS, SITE_BLOCK>((double)tr, (double)th, partials,
                                          blockIdx.x * (UPDS_THREADS / SITE_BLOCK));
 }
 
 void update_set_max_lds() {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_update_shared32<128>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)upds_lds<128>());
+    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_update_shared<float, float, 128, false>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)upds_lds<float, 128>());
 }
 
 // reorder 4 fields between natural index order and transform-position order
@@ -997,15 +1021,18 @@ hipError_t launch_update(const geom &g, const void *Lin, void *Lout, const void 
         if constexpr (ACC) {
             // links G U0 G^dagger from the constant copy U0 (Lin), not stored
             if (update_shared_ok(g)) {
-                auto shared = [&](auto xy) {
+                auto shared = [&](auto xy, auto stream) {
                     constexpr int XY = decltype(xy)::value;
-                    k_update_shared32<XY>
-                        <<<(unsigned)(g.V / (XY * UPDS_T)), XY * UPDS_T, upds_lds<XY>(), st>>>(
+                    k_update_shared<float, float, XY, decltype(stream)::value>
+                        <<<(unsigned)(g.V / (XY * UPDS_T)), XY * UPDS_T, upds_lds<float, XY>(), st>>>(
                             g, static_cast<const float2 *>(Lin), static_cast<const float2 *>(GX),
                             static_cast<float2 *>(Dout), partials, status);
                 };
-                if (g.V < UPDS_SPLIT_SITES) shared(std::integral_constant<int, 64>{});
-                else shared(std::integral_constant<int, 128>{});
+                using N64 = std::integral_constant<int, 64>;
+                using N128 = std::integral_constant<int, 128>;
+                if (g.V < UPDS_SPLIT_SITES) shared(N64{}, std::false_type{});
+                else if (upds_stream(g)) shared(N128{}, std::true_type{});
+                else shared(N128{}, std::false_type{});
                 return hipGetLastError();
             }
             if (g.lf == 18) go(k_update<T, TF, true, 18, false>);
@@ -1088,7 +1115,17 @@ hipError_t launch_update_u0(const geom &g, const void *U0, const void *G, void *
                                                         static_cast<const double2 *>(G), D,
                                                         partials, status);
     };
-    if (g.ff32) go(k_update_u0<float>, static_cast<float2 *>(Dout));
+    auto shared = [&](auto *D) {
+        using TF = decltype(D->x);
+        k_update_shared<double, TF, 64, false>
+            <<<(unsigned)(g.V / SITE_BLOCK), SITE_BLOCK, upds_lds<double, 64>(), st>>>(
+                g, static_cast<const double2 *>(U0), static_cast<const double2 *>(G), D, partials,
+                status);
+    };
+    if (update_shared64_ok(g)) {
+        if (g.ff32) shared(static_cast<float2 *>(Dout));
+        else shared(static_cast<double2 *>(Dout));
+    } else if (g.ff32) go(k_update_u0<float>, static_cast<float2 *>(Dout));
     else go(k_update_u0<double>, static_cast<double2 *>(Dout));
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

@@ -87,3 +87,12 @@ def test_resume_to_rounding(lgf_gpu):
     lgf_gpu.iterate(b, ALPHA, 2)
     lgf_gpu.iterate(b, ALPHA, 3)
     assert np.max(np.abs(cpu(a) - cpu(b))) < 5e-13
+
+
+# from 524288 sites the links are shared through LDS (blocks of 64 xy-sites x 4
+# t): rows of one block, rows that straddle blocks, rows longer than a block;
+# one row below the rule's volume
+@pytest.mark.parametrize("L", [(64, 32, 16, 16), (48, 32, 8, 48), (128, 16, 16, 16),
+                               (64, 32, 16, 12)])
+def test_three_sweeps_shared_links(lgf_gpu, L):
+    test_three_sweeps(lgf_gpu, L, {})
