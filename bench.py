@@ -557,7 +557,7 @@ def main() -> int:
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                      "traffic": measured_traffic(),
-                     "kernel": "k_update_u0<double> (links from U0 and G, next divergence)",
+                     "kernel": "k_update_shared<double> (links from U0 and G, next divergence)",
                      "bytes_per_site": BYTES_PER_SITE["fp64"]["update"]},
         "sweep_roofline_frac": round(sum(BYTES_PER_SITE["fp64"].values()) * V * ips / 1e9 /
                                      HBM_PEAK_GBS, 4),

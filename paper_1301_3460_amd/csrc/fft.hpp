@@ -44,10 +44,15 @@ __host__ __device__ constexpr int fft_reg_span(int n) {
 // that of the heaviest transform it holds.  Tier 16: one-pass extents up to
 // 16 and two-pass extents N1 x N2 with N1 <= 8, N2 <= 12 (36 = 6x6,
 // 48 = 6x8, 54 = 6x9, 64 = 8x8, 72 = 8x9, 96 = 8x12), which fit 128 VGPRs
-// in every pass kernel; tier 32: the rest.
+// in every pass kernel; tier 24: registers for at most 24 values (18, 24 and
+// the two-pass extents up to 256 = 16x16 but 243 = 9x27); tier 32: the rest.
+// Tier 24 has instances of the two-axis tiles only (FP64 160 to 190 VGPRs
+// there against 256, FP32 about 100); the other kernels run it in their tier
+// 32 instance.
 __host__ __device__ constexpr int fft_tier(int n) {
-    return n <= 32 ? (n <= 16 ? 16 : 32)
-                   : ((fft_split(n) <= 8 && n / fft_split(n) <= 12) ? 16 : 32);
+    const int n1 = fft_split(n), n2 = n / n1;
+    if (n <= 16 || (n > 32 && n1 <= 8 && n2 <= 12)) return 16;
+    return n2 <= 24 ? 24 : 32;
 }
 
 __host__ __device__ constexpr bool fft_supported(int n) {
@@ -134,8 +139,22 @@ LGF_HD void dft(cpx<T> *a, const vec2_t<T> *__restrict__ tw) {
     }
 }
 
+// w / ncols for w below 2^20 (an LDS tile holds at most 20480 elements), from
+// rcols = 1/ncols: w + 1/2 is at least 1/(2 ncols) of a quotient away from the
+// next integer, its error below w/ncols * 2^-21.  An integer division costs
+// five times the instructions (48 x 48 planes in FP32: 30.5 against 29.6 µs).
+LGF_HD int div_cols(int w, float rcols) { return (int)(((float)w + 0.5f) * rcols); }
+
 // Column c of the tile: elements lds[base(c) + j*stride], j < N.
 // Must be called by every thread of the block (two-pass extents synchronise).
+// In both passes of a two-pass extent consecutive threads take consecutive
+// columns of one part (n2 or k1), not consecutive parts of one column: parts
+// lie N2 (or one) strides apart, a multiple of the 128 bytes LDS serves per
+// cycle for most extents, and 70% of the LDS cycles of the FP64 48^3 x 96
+// middle pass were bank conflicts; a wave also reads few twiddles.  Columns are
+// consecutive or, between rows of a tile, at the distances the plans pad for
+// (plan_tile2).  48^3 x 96: FP64 middle pass 608 -> 545 µs, FP32 364 -> 333;
+// FP64 first pass 326 -> 305.
 template <int N, int DIR, class T, class Base>
 LGF_HD void lds_axis_fft_n(vec2_t<T> *lds, int ncols, int stride, Base base,
                            const vec2_t<T> *__restrict__ tw) {
@@ -152,11 +171,12 @@ LGF_HD void lds_axis_fft_n(vec2_t<T> *lds, int ncols, int stride, Base base,
         }
     } else {
         constexpr int N1 = fft_split(N), N2 = N / N1;
+        const float rcols = 1.0f / (float)ncols;
         static_assert(N1 * N2 == N && N1 > 1, "unsupported extent");
         if constexpr (DIR < 0) {
             // pass 1: for each n2, DFT_N1 over n1 (stride N2), times W_N^(n2 k1)
             for (int w = threadIdx.x; w < ncols * N2; w += nthr) {
-                const int c = w / N2, n2 = w - c * N2;
+                const int n2 = div_cols(w, rcols), c = w - n2 * ncols;
                 const int b0 = base(c) + n2 * stride;
                 cpx<T> a[N1];
 #pragma unroll
@@ -170,7 +190,7 @@ LGF_HD void lds_axis_fft_n(vec2_t<T> *lds, int ncols, int stride, Base base,
             __syncthreads();
             // pass 2: for each k1, DFT_N2 over n2 (contiguous block of N2)
             for (int w = threadIdx.x; w < ncols * N1; w += nthr) {
-                const int c = w / N1, k1 = w - c * N1;
+                const int k1 = div_cols(w, rcols), c = w - k1 * ncols;
                 const int b0 = base(c) + k1 * N2 * stride;
                 cpx<T> a[N2];
 #pragma unroll
@@ -182,7 +202,7 @@ LGF_HD void lds_axis_fft_n(vec2_t<T> *lds, int ncols, int stride, Base base,
         } else {
             // undo pass 2: for each k1, inverse DFT_N2 over the block, times W_N^(-n2 k1)
             for (int w = threadIdx.x; w < ncols * N1; w += nthr) {
-                const int c = w / N1, k1 = w - c * N1;
+                const int k1 = div_cols(w, rcols), c = w - k1 * ncols;
                 const int b0 = base(c) + k1 * N2 * stride;
                 cpx<T> a[N2];
 #pragma unroll
@@ -196,7 +216,7 @@ LGF_HD void lds_axis_fft_n(vec2_t<T> *lds, int ncols, int stride, Base base,
             __syncthreads();
             // undo pass 1: for each n2, inverse DFT_N1 over k1 (stride N2)
             for (int w = threadIdx.x; w < ncols * N2; w += nthr) {
-                const int c = w / N2, n2 = w - c * N2;
+                const int n2 = div_cols(w, rcols), c = w - n2 * ncols;
                 const int b0 = base(c) + n2 * stride;
                 cpx<T> a[N1];
 #pragma unroll
@@ -240,10 +260,11 @@ LGF_HD void lds_axis_fsi_n(vec2_t<T> *lds, int ncols, int stride, Base base, Pre
         }
     } else {
         constexpr int N1 = fft_split(N), N2 = N / N1;
+        const float rcols = 1.0f / (float)ncols;
         static_assert(N1 * N2 == N && N1 > 1, "unsupported extent");
         // forward pass 1: for each n2, DFT_N1 over n1 (stride N2), times W_N^(n2 k1)
         for (int w = threadIdx.x; w < ncols * N2; w += nthr) {
-            const int c = w / N2, n2 = w - c * N2;
+            const int n2 = div_cols(w, rcols), c = w - n2 * ncols;
             const int b0 = base(c) + n2 * stride;
             cpx<T> a[N1];
 #pragma unroll
@@ -258,7 +279,7 @@ LGF_HD void lds_axis_fsi_n(vec2_t<T> *lds, int ncols, int stride, Base base, Pre
         // per k1: forward DFT_N2 (position k1 N2 + k2), scaling, inverse DFT_N2,
         // times W_N^(-n2 k1)
         for (int w = threadIdx.x; w < ncols * N1; w += nthr) {
-            const int c = w / N1, k1 = w - c * N1;
+            const int k1 = div_cols(w, rcols), c = w - k1 * ncols;
             const int b0 = base(c) + k1 * N2 * stride;
             const auto info = prep(c);
             cpx<T> a[N2];
@@ -280,7 +301,7 @@ LGF_HD void lds_axis_fsi_n(vec2_t<T> *lds, int ncols, int stride, Base base, Pre
         __syncthreads();
         // inverse pass 1: for each n2, inverse DFT_N1 over k1 (stride N2)
         for (int w = threadIdx.x; w < ncols * N2; w += nthr) {
-            const int c = w / N2, n2 = w - c * N2;
+            const int n2 = div_cols(w, rcols), c = w - n2 * ncols;
             const int b0 = base(c) + n2 * stride;
             cpx<T> a[N1];
 #pragma unroll

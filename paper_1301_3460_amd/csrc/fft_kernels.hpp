@@ -295,9 +295,11 @@ __global__ void __launch_bounds__(AXIS_BLOCK) __attribute__((amdgpu_waves_per_eu
 
 // NTHR: threads per block; at the lighter register tier 512 where two tiles
 // share a compute unit and 1024 where one tile fills it (16 waves either
-// way), 256 at the wider tier
+// way), 256 at the wider tiers.  The waves bound keeps the FP64 middle pass of
+// tier 16 at 128 VGPRs: at 130 only one 512-thread block fits a compute unit
+// (48^3 x 96: 0.80 against 0.55 ms).
 template <class T, int MODE, int RMAX, int NTHR>
-__global__ void __launch_bounds__(NTHR)
+__global__ void __launch_bounds__(NTHR) __attribute__((amdgpu_waves_per_eu(RMAX <= 16 ? 4 : 1)))
     k_fft_tile2(geom g, vec2_t<T> *__restrict__ D, const vec2_t<T> *__restrict__ tw,
                 const T *__restrict__ ptab, T p2max_over_V, tile2_plan tp,
                 const dev_status *__restrict__ status, fold_args fold) {
@@ -316,28 +318,28 @@ __global__ void __launch_bounds__(NTHR)
     const int nel = W * Na * Nb;
     // Loads per thread in flight in the copies, as measured at 48^3 x 96:
     // nine (0.33 against 0.41 ms in the FP64 first pass), three in the FP32
-    // first pass (0.17 against 0.20), one in the FP64 middle pass, whose
-    // 32-byte rows are shared by four blocks (0.68 ms; 0.94 with nine loads,
-    // 0.73 with nine loads and nine stores, 0.92 with three of each).  Stores
-    // are batched in the first pass only (the FP64 last pass: 0.34 ms with
-    // single stores, 0.37 batched).
+    // first pass (0.17 against 0.20), nine in the FP32 middle pass (0.32
+    // against 0.36 with one), one in the FP64 middle pass, whose 32-byte rows
+    // are shared by four blocks (0.545 ms; 0.563 with two, 0.569 with four);
+    // wider rows take four.  Stores are batched in the first pass only (the
+    // FP64 last pass: 0.34 ms with single stores, 0.37 batched).
     constexpr int CHL = (MODE == 0 && sizeof(T) == 8) ? 1 : (MODE < 0 && sizeof(T) == 4) ? 3 : 9;
     constexpr int CHS = MODE < 0 ? CHL : 1;
     // tile digits (w, ja, jb); a padding column of a ragged group reads its
     // group's last column and stores zero
     auto hbm = [=](const tile_idx &p) { return F + ((unsigned)p.b * sa + (unsigned)p.c * sb + (unsigned)p.a); };
     auto sh = [=](const tile_idx &p) { return lds + (p.a + p.b * PA + p.c * PB); };
-    tile_copy<NTHR, CHL, vec2_t<T>>(
-        nel, W, Na,
-        [=](const tile_idx &p) {
-            tile_idx q = p;
-            q.a = min(q.a, Wt - 1);
-            return *hbm(q);
-        },
-        [=](const tile_idx &p, vec2_t<T> v) {
-            if (p.a >= Wt) v.x = v.y = T(0);
-            *sh(p) = v;
-        });
+    auto get = [=](const tile_idx &p) {
+        tile_idx q = p;
+        q.a = min(q.a, Wt - 1);
+        return *hbm(q);
+    };
+    auto put = [=](const tile_idx &p, vec2_t<T> v) {
+        if (p.a >= Wt) v.x = v.y = T(0);
+        *sh(p) = v;
+    };
+    if (CHL == 1 && W * sizeof(vec2_t<T>) > 32) tile_copy<NTHR, 4, vec2_t<T>>(nel, W, Na, get, put);
+    else tile_copy<NTHR, CHL, vec2_t<T>>(nel, W, Na, get, put);
     __syncthreads();
     const vec2_t<T> *twa = tw + tp.ta, *twb = tw + tp.tb;
     auto cola = [W, PB](int c) { return (c % W) + (c / W) * PB; };  // c = w + W*jb
@@ -841,13 +843,19 @@ template <class T> void plan_two_tile(const geom &g, int ncu, fft_plan &p) {
         p.lds_zt2 = p.lds + (size_t)(g.Lx + g.Ly + g.Lz + g.Lt) * sizeof(T);
 }
 
-// (x,t) planes and (y,z) tiles of 32-byte rows (2 FP64 or 4 FP32 x-sites),
-// for an extent above 32 in (z,t), where both tiles fit and the planes' rows
-// are at least 16 sites.
+// (x,t) planes and (y,z) tiles of W x-sites, for an extent above 32 in (z,t),
+// where both tiles fit and the planes' rows are at least 16 sites.  W: the
+// widest divisor of Lx up to 8 sites, in rows of whole 32 bytes, whose tile
+// leaves room for a second one on the compute unit (48 x 48: 2 FP64 or 4 FP32
+// sites); 32-byte rows where none does.  FP64 middle pass of 24^3 x 48 and
+// 48 x 24 x 24 x 48: 62 and 101 µs at 2 sites, 48 and 73 at 4, 42 and 61 at 8.
+// FP32: 29 and 38 at 4, 26 and 35 at 8, 31 and 50 at 12.  LDS strides: the distance of b-rows is W modulo the 128 bytes LDS
+// serves per cycle (odd for the planes), so that consecutive columns along
+// either axis fall on different banks.
 template <class T> void plan_tile2(const geom &g, size_t budget, fft_plan &p) {
     if (p.rc) return;
-    constexpr int TILE2_W = 32 / (int)sizeof(vec2_t<T>);
     const size_t e = sizeof(vec2_t<T>);
+    const int M = 128 / (int)e;  // elements per LDS cycle
     const long Lxy = (long)g.Lx * g.Ly, Lxyz = Lxy * g.Lz;
     const int ox = 0, oy = g.Lx, oz = g.Lx + g.Ly, ot = g.Lx + g.Ly + g.Lz;
     tile2_plan a;  // (x,t) planes: a = x (the rows), b = t; slices (y,z)
@@ -861,7 +869,7 @@ template <class T> void plan_tile2(const geom &g, size_t budget, fft_plan &p) {
     a.nouter = g.Ly * g.Lz;
     a.so = g.Lx;
     a.PA = 1;
-    a.PB = g.Lx + 1;
+    a.PB = g.Lx | 1;
     a.ta = ox;
     a.tb = ot;
     a.rmax = std::max(fft_tier(g.Lx), fft_tier(g.Lt));
@@ -870,21 +878,36 @@ template <class T> void plan_tile2(const geom &g, size_t budget, fft_plan &p) {
     tile2_plan b;  // (y,z) tiles: W x-sites, a = y, b = z; slices t
     b.Na = g.Ly;
     b.Nb = g.Lz;
-    b.W = TILE2_W;
     b.sa = g.Lx;
     b.sb = Lxy;
     b.R = g.Lx;
-    b.ngrp = (g.Lx + TILE2_W - 1) / TILE2_W;
     b.nouter = g.Lt;
     b.so = Lxyz;
-    b.PA = TILE2_W;
-    b.PB = g.Ly * TILE2_W + 1;
     b.ta = oy;
     b.tb = oz;
     b.tw = ox;
     b.to = ot;
     b.rmax = std::max(fft_tier(g.Ly), fft_tier(g.Lz));
-    b.lds = (size_t)b.Nb * b.PB * e;
+    auto width = [&](int w) {
+        b.W = w;
+        b.ngrp = (g.Lx + w - 1) / w;
+        b.PA = w;
+        b.PB = g.Ly * w;
+        while (b.PB % M != w % M) ++b.PB;
+        b.lds = (size_t)b.Nb * b.PB * e;
+        // padding that costs the second tile of a compute unit, or the tile
+        // itself, is left out
+        const size_t l1 = (size_t)b.Nb * (g.Ly * w + 1) * e;
+        if ((l1 <= 80 * 1024 && b.lds > 80 * 1024) || (l1 <= 160 * 1024 && b.lds > 160 * 1024)) {
+            b.PB = g.Ly * w + 1;
+            b.lds = l1;
+        }
+        return b.lds;
+    };
+    const int w32 = 32 / (int)e;
+    int w = 8;
+    while (w > w32 && !(g.Lx % w == 0 && width(w) <= budget)) w -= w32;
+    width(w);
     b.nthr = b.lds > 80 * 1024 ? 1024 : 512;
     if (g.Lx < 16 || a.lds > budget || b.lds > 160 * 1024 || a.nouter > 65535) return;
     p.t2 = true;
@@ -947,7 +970,8 @@ hipError_t launch_tile2(const geom &g, vec2_t<T> *D, const vec2_t<T> *tw, const 
     const dim3 grid = tile2_grid(a, g.nf);
 #define LGF_T2(R, N)                                                                               \
     k_fft_tile2<T, MODE, R, N><<<grid, N, a.lds, st>>>(g, D, tw, ptab, p2max_over_V, a, status, fold)
-    if (a.rmax > 16) LGF_T2(32, 256);
+    if (a.rmax > 24) LGF_T2(32, 256);
+    else if (a.rmax > 16) LGF_T2(24, 256);
     else if (a.nthr == 1024) LGF_T2(16, 1024);
     else LGF_T2(16, 512);
 #undef LGF_T2
@@ -1000,6 +1024,7 @@ template <class T> void fft_set_max_lds(const geom &g, const fft_plan &p) {
 #define LGF_T2S(M)                                                                   \
     set(reinterpret_cast<const void *>(&k_fft_tile2<T, M, 16, 512>), b);            \
     set(reinterpret_cast<const void *>(&k_fft_tile2<T, M, 16, 1024>), b);           \
+    set(reinterpret_cast<const void *>(&k_fft_tile2<T, M, 24, 256>), b);            \
     set(reinterpret_cast<const void *>(&k_fft_tile2<T, M, 32, 256>), b);
         LGF_T2S(-1) LGF_T2S(0) LGF_T2S(1)
 #undef LGF_T2S
@@ -1008,6 +1033,8 @@ template <class T> void fft_set_max_lds(const geom &g, const fft_plan &p) {
             if (a4 <= XY_ACC_LDS_MAX) {
                 set(reinterpret_cast<const void *>(&k_fft_tile2_acc<16, true>), a4);
                 set(reinterpret_cast<const void *>(&k_fft_tile2_acc<16, false>), a4);
+                set(reinterpret_cast<const void *>(&k_fft_tile2_acc<24, true>), a4);
+                set(reinterpret_cast<const void *>(&k_fft_tile2_acc<24, false>), a4);
                 set(reinterpret_cast<const void *>(&k_fft_tile2_acc<32, true>), a4);
                 set(reinterpret_cast<const void *>(&k_fft_tile2_acc<32, false>), a4);
             }
@@ -1140,6 +1167,9 @@ hipError_t launch_fft_xy_inv_acc(const geom &g, void *D, const void *tw, const f
             if (pl.t2a.rmax <= 16) {
                 if (exact) LGF_TA(16, true);
                 else LGF_TA(16, false);
+            } else if (pl.t2a.rmax <= 24) {
+                if (exact) LGF_TA(24, true);
+                else LGF_TA(24, false);
             } else {
                 if (exact) LGF_TA(32, true);
                 else LGF_TA(32, false);

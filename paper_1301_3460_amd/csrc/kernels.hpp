@@ -199,7 +199,7 @@ struct fft_plan {
     // tile count still gives every compute unit two blocks
     bool xy2 = false, zt2 = false;
     size_t lds_zt2 = 0;
-    // FP64, (z,t) beyond the register columns: (x,t) planes as the first and
+    // (z,t) beyond the register columns: (x,t) planes as the first and
     // last pass (t2a) and (y,z) tiles of W x-sites as the middle pass (t2b),
     // three passes over the field instead of the five of the x,y / z / t / z /
     // x,y scheme

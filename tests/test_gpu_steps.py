@@ -115,6 +115,24 @@ def test_lockstep_sweeps_tile2(lgf_gpu, L):
     test_lockstep_sweeps(lgf_gpu, L)
 
 
+# (y,z) tiles of eight, six and four x-sites, the register tier of 24 in the
+# tiles (24, 144 = 12 x 12), in the planes (24) and beside tier 32
+# (243 = 9 x 27), a tile whose row padding would not fit LDS (18 x 256)
+TILE2_WIDE_SHAPES = [(24, 24, 3, 48), (18, 24, 36, 2), (16, 144, 2, 36), (36, 16, 24, 36),
+                     (24, 2, 4, 243), (16, 18, 256, 2)]
+
+
+@pytest.mark.parametrize("L", TILE2_WIDE_SHAPES)
+@pytest.mark.parametrize("sign", [-1, +1])
+def test_fft4d_tile2_wide(lgf_gpu, L, sign):
+    test_fft4d(lgf_gpu, L, sign)
+
+
+@pytest.mark.parametrize("L", TILE2_WIDE_SHAPES)
+def test_fourier_accelerate_tile2_wide(lgf_gpu, L):
+    test_fourier_accelerate(lgf_gpu, L)
+
+
 @pytest.mark.parametrize("L", TWO_TILE_SHAPES)
 @pytest.mark.parametrize("sign", [-1, +1])
 def test_fft4d_two_tile(lgf_gpu, L, sign):
