@@ -588,10 +588,11 @@ __global__ void __launch_bounds__(rc_max_threads<T>())
     const vec2_t<T> *twz = tw_z<T>(g, tw), *twt = tw_t<T>(g, tw);
     // A padding column of a ragged tile reads the last site (its factor is 0
     // and nothing of it is stored): a load under a condition of its own waits
-    // for the one before.  Only FP64 columns beyond 16 keep the condition: all
-    // their loads in flight at once take 301 registers and with them the second
-    // wave of a SIMD (27^4: 38 us against 28).
-    constexpr bool AT_ONCE = sizeof(T) * NT <= 128;
+    // for the one before.  Only FP64 columns beyond 12 keep the condition: all
+    // their loads in flight at once take more than 256 registers and with them
+    // the second wave of a SIMD (27^4: 38 us against 28; 32^3 x 16: 31 against
+    // 24).
+    constexpr bool AT_ONCE = sizeof(T) == 4 || NT <= 12;
     if ((!AT_ONCE || !tiles_first(g)) && status->done) return;
     vec2_t<T> *p = D + (long)blockIdx.y * g.S + (long)z * Lxy + (AT_ONCE && !live ? Lxy - 1 : s0 + w);
     const long tstride = (long)Lz * Lxy;
