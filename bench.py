@@ -51,10 +51,10 @@ BYTES_PER_SITE = {
 BYTES_XY_INV_ACC_SEPARATE = 64 + 32 + 96
 BYTES_XY_INV_ACC_SEPARATE_64 = 128 + 64 + 192
 # differentiation kernels, algorithmic bytes per site: dF/domega reads the
-# divergence of the rotated links (64) and omega (64) and writes the gradient
-# (64); dtheta/deps reads the 12-real links (384), Delta (64; neighbours
+# caller's links (576), the rotation (96) and omega (64) and writes the
+# gradient (64); dtheta/deps reads the 12-real links (384), Delta (64; neighbours
 # reused), eps (4 x 64) and writes the gradient (4 x 64)
-BYTES_OMEGA_GRAD = 3 * 64
+BYTES_OMEGA_GRAD = 4 * 144 + 96 + 64 + 64
 BYTES_THETA_GRAD = 384 + 64 + 256 + 256
 
 # sources that determine the update kernel's code (for the traffic record)
@@ -354,7 +354,7 @@ def main() -> int:
     ssf = steady_sweeps(ctx64, U0, work, args.steps)
     proff = ctx64.profile(U0, ALPHA, 20)
     e = {"sweeps_per_s": round(1.0 / ssf["s_per_sweep"], 1),
-         "per_kernel_ms": {k: round(v, 5) for k, v in proff.items()}, "bytes_per_site": 1024}
+         "per_kernel_ms": {k: round(v, 5) for k, v in proff.items()}, "bytes_per_site": 864}
     for prec, ctx in (("fp64", ctx64), ("mixed", ctx32)):
         t, res = solve_timing(ctx, U0, work, args.solves)
         e[f"solve_ms_{prec}"] = round(1e3 * t, 3)

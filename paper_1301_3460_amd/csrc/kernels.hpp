@@ -102,8 +102,9 @@ inline geom make_geom(const int L[4], int nc) {
 // other two passes 128 each) where one that stores its links moves 1280, but
 // its inverse pass also reads and writes G: per sweep, stored links against
 // U0 and G, 48.0 / 49.3 us at 18^2 x 12 x 9 (34992 sites), 53.0 / 50.0 at 16^4,
-// 74.8 / 66.6 at 16^3 x 32, 135 / 109 at 24^4, 290 / 284 at 32^4 and
-// 1783 / 1752 at 48^4, whose inverse (x,t) pass leaves G to a kernel of its own.
+// 74.8 / 66.6 at 16^3 x 32, 135 / 109 at 24^4, and with the update that shares
+// links through LDS 290 / 257 at 32^4 and 3370 / 3207 at 48^3 x 96, whose inverse
+// (x,t) pass leaves G to a kernel of its own.
 constexpr long KEEP_U0_MIN_SITES = 49152;
 inline bool geom::keeps_u0() const { return nc == 3 && lf == 12 && V >= KEEP_U0_MIN_SITES; }
 

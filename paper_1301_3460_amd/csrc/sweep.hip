@@ -10,11 +10,16 @@
 //               Delta(x) from U'_mu(x) and the recomputed U'_mu(x-mu), with
 //               block partial sums of F and theta
 //   finalize    fixed-order sum of the partials, stopping test
-// Links are double-buffered (the update reads U_mu(x-mu) of other threads),
-// as are the Fourier fields.  The FP32 sweeps of an SU(3) mixed solve store
-// no links: their inverse (x, y) pass (or k_gauge_acc after it) turns L Delta
-// into G <- g G, double-buffered, and the update forms G U0 G^dagger from the
-// constant input copy U0.
+// The form above stores the links of every sweep (double-buffered, as the
+// update reads U_mu(x-mu) of other threads): SU(2), 8- and 18-real links and
+// FP64 sweeps below 49152 sites.  The FP64 sweeps of larger lattices and the
+// FP32 sweeps of an SU(3) mixed solve store no links: their inverse (x, y)
+// pass (or k_gauge_acc after it) turns L Delta into G <- g G, double-buffered,
+// and the update (k_update_u0, k_update_shared) forms G U0 G^dagger from the
+// constant input copy U0; k_unpack_rotated writes them once, at the end.
+// Small lattices run the four transforms of a field in one block (fft_small.hip),
+// take a lane per link in the update (k_update_dirs) and finalize inside the
+// next sweep's first kernel.
 #include <type_traits>
 
 #include "common.hpp"
