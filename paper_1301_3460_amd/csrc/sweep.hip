@@ -368,19 +368,30 @@ __global__ void __launch_bounds__(SITE_BLOCK)
 // The next Delta and the partials of F and theta of the links
 // U_mu(x) = G(x) U0_mu(x) G(x+mu)^dagger, which are formed and not stored: 544
 // bytes per site (R U0 384, R G 96, W Delta 64) instead of the 896 of k_update
-// (R links, W links, R L Delta, W Delta).  With
-//   K(x) = sum_mu [U0_mu(x) G(x+mu)^dagger + (G(x-mu) U0_mu(x-mu))^dagger]
-// the sum over mu of U_mu(x) + U_mu(x-mu)^dagger is M = G(x) K(x), so that
-// X - X^dagger = M^dagger - M and the eight links need nine matrix products
-// instead of sixteen; sum_mu Re Tr U_mu over the lattice is half that of M.
-// Each product is a matrix of SU(3): rows 0,1 by products, row 2 completed.
-// At 32^4 146 us against 195 for k_update (event timing; 725 MB of measured
-// traffic against 1060).  Its time is that of its reads: a kernel that only
+// (R links, W links, R L Delta, W Delta).  They are the links that
+// k_unpack_rotated returns, rows 0,1 by products and row 2 completed from them,
+// also where U0 is in SU(3) only to the precision it was stored in.  With q(A)
+// for rows 0,1 of A and their completion, and as completing commutes with an
+// SU(3) factor on the right,
+//   sum_mu U_mu(x-mu)^dagger = G(x) sum_mu q(G(x-mu) U0_mu(x-mu))^dagger
+// while of the links leaving x, with p = q(U0 G(x+mu)^dagger), rows 0,1 are
+// those of G(x) p and row 2 is that of G(x) p', p' the conjugate cofactors of p
+// (p itself in SU(3); always p's third row).  So the sum over mu of U_mu(x) +
+// U_mu(x-mu)^dagger is M with rows 0,1 of G(x) K(x) and row 2 of G(x) K'(x),
+// K and K' the sums of the q^dagger with the p and with the p', X - X^dagger =
+// M^dagger - M, and the eight links need nine matrix products instead of
+// sixteen; sum_mu Re Tr U_mu over the lattice is half that of M.  Row 2 from K
+// as well (the links formed in SU(3) throughout) makes a solve of links rounded
+// to FP32 stop at theta = 7e-16 of M where the returned links have 2e-15, and
+// saves 1% (27^4 85.7 against 86.1 us, 24^4 43.5 against 44.5).
+// With K alone at 32^4 146 us against 195 for k_update (event timing; 725 MB of
+// measured traffic against 1060): the time of its reads, as a kernel that only
 // streams U0 and G and writes Delta takes 122 us, and one whose eight
-// neighbours are its own site 142.  206 VGPRs, two waves per SIMD: with three
+// neighbours are its own site 142.  222 VGPRs, two waves per SIMD: with three
 // (168 VGPRs) 152 us, with four and no load ahead 169, as more blocks in
 // flight find fewer neighbour lines in L2.  Marking the loads of U0 as
-// streaming costs the L2 reuse of U0(x-mu): 171 us.
+// streaming costs the L2 reuse of U0(x-mu): 171 us.  Taking the arriving links
+// before the leaving ones costs reuse too (24^4 52, 27^4 92 us).
 template <class TF>
 __global__ void __launch_bounds__(SITE_BLOCK)
     k_update_u0(geom g, const double2 *__restrict__ U0, const double2 *__restrict__ G,
@@ -416,8 +427,11 @@ __global__ void __launch_bounds__(SITE_BLOCK)
         half d[2];
         fetch(0, d[0]);
         mat3<T> K;
+        cpx<T> C[2][3];  // rows 0,1 of K' (row 2 is that of K)
 #pragma unroll
         for (int k = 0; k < 9; ++k) K.e[k / 3][k % 3] = mk<T>(0, 0);
+#pragma unroll
+        for (int k = 0; k < 6; ++k) C[k / 3][k % 3] = mk<T>(0, 0);
 #pragma unroll
         for (int h = 0; h < 8; ++h) {
             if (h < 7) fetch(h + 1, d[(h + 1) & 1]);
@@ -438,6 +452,14 @@ __global__ void __launch_bounds__(SITE_BLOCK)
 #pragma unroll
                 for (int k = 0; k < 9; ++k)
                     K.e[k / 3][k % 3] = K.e[k / 3][k % 3] + p.e[k / 3][k % 3];
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int j = 0; j < 3; ++j) {
+                        const int r = i + 1, t = (i + 2) % 3, a = (j + 1) % 3, b = (j + 2) % 3;
+                        const cpx<T> m = cmul(p.e[r][a], p.e[t][b]);
+                        C[i][j] = C[i][j] + conjg(cmsub(m, p.e[r][b], p.e[t][a]));
+                    }
             } else {
                 rebuild_row2(u);  // rows 0,1 of G U0 need rows 0,1 of G
 #pragma unroll
@@ -452,27 +474,30 @@ __global__ void __launch_bounds__(SITE_BLOCK)
 #pragma unroll
                 for (int k = 0; k < 9; ++k)
                     K.e[k / 3][k % 3] = K.e[k / 3][k % 3] + conjg(p.e[k % 3][k / 3]);
+#pragma unroll
+                for (int k = 0; k < 6; ++k)
+                    C[k / 3][k % 3] = C[k / 3][k % 3] + conjg(p.e[k % 3][k / 3]);
             }
         }
         mat3<T> g0;
 #pragma unroll
         for (int k = 0; k < 6; ++k) g0.e[k / 3][k % 3] = ld<T>(G + (long)k * g.S + s);
         rebuild_row2(g0);
-        xacc<T> X;
-        xacc_zero(X);
         mat3<T> M;
 #pragma unroll
         for (int i = 0; i < 3; ++i)
 #pragma unroll
             for (int j = 0; j < 3; ++j) {
-                cpx<T> a = cmul(g0.e[i][0], K.e[0][j]);
-                a = cmac(a, g0.e[i][1], K.e[1][j]);
+                cpx<T> a = cmul(g0.e[i][0], i < 2 ? K.e[0][j] : C[0][j]);
+                a = cmac(a, g0.e[i][1], i < 2 ? K.e[1][j] : C[1][j]);
                 M.e[i][j] = cmac(a, g0.e[i][2], K.e[2][j]);
             }
+        xacc<T> X;
+        xacc_zero(X);
         xacc_add(X, M, T(-1));
+        fs = 0.5 * retrace(M);
         cpx<T> f0, f1, f2, f3;
         ts = delta_pack(X, f0, f1, f2, f3);
-        fs = 0.5 * retrace(M);
         st_stream<TF>(Dout + s, cvt<TF>(f0));
         st_stream<TF>(Dout + g.S + s, cvt<TF>(f1));
         st_stream<TF>(Dout + 2 * g.S + s, cvt<TF>(f2));
