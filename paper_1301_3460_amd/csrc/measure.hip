@@ -370,9 +370,11 @@ __global__ void __launch_bounds__(SITE_BLOCK)
     block_sum2<SITE_BLOCK>(acc, 0.0, partials, blockIdx.x);
 }
 
-// F_U[G] partials and dF/domega^a(x) in one pass: Delta of the rotated links
-// from M = G(x) K(x) (K as in k_update_u0), then the derivative of the
-// exponential map at omega(x).
+// F_U[G] partials and dF/domega^a(x) in one pass: Delta of the rotated links,
+// rows 0,1 formed and row 2 completed, from M of K and K' as in k_update_u0 (row
+// 2 from K as well is off on links rounded to FP32), then the derivative of the
+// exponential map at omega(x).  240 VGPRs, two waves per SIMD; without K', at 154
+// and three, F and gradient of 32^4 took 395 us instead of 293.
 //   G^b = -(i/4) normF Tr[lambda_b Delta] = (normF/4) Im Tr[lambda_b Delta]
 __global__ void __launch_bounds__(SITE_BLOCK)
     k_omega_grad(geom g, aos_links L, soa_links G, const double *__restrict__ om,
@@ -382,8 +384,11 @@ __global__ void __launch_bounds__(SITE_BLOCK)
     if (s < g.V) {
         const nbr n = neighbours(g, s);
         mat3<double> K;
+        cpx<double> C[2][3];  // rows 0,1 of K'
 #pragma unroll
         for (int k = 0; k < 9; ++k) K.e[k / 3][k % 3] = mk<double>(0, 0);
+#pragma unroll
+        for (int k = 0; k < 6; ++k) C[k / 3][k % 3] = mk<double>(0, 0);
         // one direction's 24 loads at a time: unrolled, the compiler issues all
         // 102 first, which takes 456 registers and leaves one wave per SIMD
 #pragma unroll 1
@@ -398,8 +403,23 @@ __global__ void __launch_bounds__(SITE_BLOCK)
 #pragma unroll
             for (int k = 0; k < 9; ++k)
                 K.e[k / 3][k % 3] = K.e[k / 3][k % 3] + (p.e[k / 3][k % 3] + conjg(q.e[k % 3][k / 3]));
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 3; ++j) {
+                    const int r = i + 1, t = (i + 2) % 3, a = (j + 1) % 3, b = (j + 2) % 3;
+                    const cpx<double> m = cmul(p.e[r][a], p.e[t][b]);
+                    C[i][j] = C[i][j] + conjg(cmsub(m, p.e[r][b], p.e[t][a]) + q.e[j][i]);
+                }
         }
-        const mat3<double> M = mat_mul_full(link_at(G, 0, s), K);
+        const mat3<double> g0 = link_at(G, 0, s);
+        mat3<double> M = mat_mul_full(g0, K);
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            cpx<double> c = cmul(g0.e[2][0], C[0][j]);
+            c = cmac(c, g0.e[2][1], C[1][j]);
+            M.e[2][j] = cmac(c, g0.e[2][2], K.e[2][j]);
+        }
         xacc<double> X;
         xacc_zero(X);
         xacc_add(X, M, -1.0);
