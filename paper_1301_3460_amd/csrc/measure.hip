@@ -278,6 +278,8 @@ __global__ void __launch_bounds__(SITE_BLOCK)
 
 // sum_{mu<nu} Re Tr[U_mu(x) U_nu(x+mu) U_mu(x+nu)^dagger U_nu(x)^dagger]
 //   = Re Tr[P Q^dagger], P = U_mu(x) U_nu(x+mu), Q = U_nu(x) U_mu(x+nu)
+// All three rows by products: a completed row 2 is not the product's on links
+// in SU(3) only to the precision they were stored in.
 __global__ void __launch_bounds__(SITE_BLOCK)
     k_plaquette(geom g, aos_links L, double *__restrict__ partials) {
     const long s = block_site(g, blockIdx.x, gridDim.x, threadIdx.x);
@@ -289,8 +291,8 @@ __global__ void __launch_bounds__(SITE_BLOCK)
             const mat3<double> u = link_at(L, mu, s);
 #pragma unroll
             for (int nu = mu + 1; nu < 4; ++nu)
-                acc += re_tr_dag(su3_mul(u, link_at(L, nu, n.p[mu])),
-                                 su3_mul(link_at(L, nu, s), link_at(L, mu, n.p[nu])));
+                acc += re_tr_dag(mat_mul_full(u, link_at(L, nu, n.p[mu])),
+                                 mat_mul_full(link_at(L, nu, s), link_at(L, mu, n.p[nu])));
         }
     }
     block_sum2<SITE_BLOCK>(acc, 0.0, partials, blockIdx.x);
@@ -355,7 +357,8 @@ __global__ void __launch_bounds__(256)
     for (int k = 0; k < 6; ++k) st<double>(p + (long)k * S, r.e[k / 3][k % 3]);
 }
 
-// F_U[G] partials: sum_mu Re Tr[G(x) U_mu(x) G(x+mu)^dagger]
+// F_U[G] partials: sum_mu Re Tr[G(x) U_mu(x) G(x+mu)^dagger] (all three rows of
+// G U by products, as in k_plaquette)
 __global__ void __launch_bounds__(SITE_BLOCK)
     k_functional_rot(geom g, aos_links L, soa_links G, double *__restrict__ partials) {
     const long s = block_site(g, blockIdx.x, gridDim.x, threadIdx.x);
@@ -365,7 +368,7 @@ __global__ void __launch_bounds__(SITE_BLOCK)
         const mat3<double> g0 = link_at(G, 0, s);
 #pragma unroll
         for (int mu = 0; mu < 4; ++mu)
-            acc += re_tr_dag(su3_mul(g0, link_at(L, mu, s)), link_at(G, 0, n.p[mu]));
+            acc += re_tr_dag(mat_mul_full(g0, link_at(L, mu, s)), link_at(G, 0, n.p[mu]));
     }
     block_sum2<SITE_BLOCK>(acc, 0.0, partials, blockIdx.x);
 }

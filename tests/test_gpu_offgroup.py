@@ -5,11 +5,13 @@ The library reads rows 0 and 1 of a link and completes row 2 = conj(row0 x
 row1).  On such links the order of completing and multiplying matters at the
 deviation from SU(3) (1e-8 here), so the results are held to their definition
 with the links so completed: F and theta of a solve are those of the links it
-returns, a gradient's links are rotated and then completed.
+returns, a gradient's links are rotated and then completed, F_U[g] and the
+plaquette are products of three rows.
 
-Bars: FP64 rounding, as for links in SU(3) (1e-14 on F, 1e-12 relative on theta
-far from the solution and on gradients).  At theta = 1e-15 the entries of Delta
-are about 3e-8, rounding errors in them 1e-15, so theta is held to 1e-6.
+Bars: FP64 rounding, as for links in SU(3) (1e-14 on F and the plaquette, 1e-12
+relative on theta far from the solution and on gradients).  At theta = 1e-15 the
+entries of Delta are about 3e-8, rounding errors in them 1e-15, so theta is held
+to 1e-6.
 """
 import numpy as np
 import pytest
@@ -121,3 +123,21 @@ def test_omega_gradient_of_the_rotated_links(lgf_gpu):
     Fg, dF = lgf_gpu._ctx(gpu(U)).functional_omega_grad(gpu(U), gpu(om))
     assert Fg == pytest.approx(F, abs=1e-14)
     assert np.max(np.abs(cpu(dF) - grad)) < 1e-12 * np.max(np.abs(grad))
+
+
+def test_products_of_three_rows(lgf_gpu):
+    L = (4, 6, 4, 8)
+    V = int(np.prod(L))
+    U = fp32_links(L, 83)
+    om = inputs.random_omega(L, 0.3, 84)
+    Uc = completed(U)
+    g = expm(0.5j * np.tensordot(om, gell_mann(), (-1, 0)))
+    F = sum(np.trace(g @ Uc[mu] @ dag(ahead(g, mu)), axis1=-2, axis2=-1).real.sum()
+            for mu in range(4)) / (12 * V)
+    P = sum(np.trace(Uc[mu] @ ahead(Uc[nu], mu) @ dag(Uc[nu] @ ahead(Uc[mu], nu)),
+                     axis1=-2, axis2=-1).real.sum()
+            for mu in range(4) for nu in range(mu + 1, 4)) / (18 * V)
+    Ug = gpu(U)
+    assert lgf_gpu._ctx(Ug).functional_omega(Ug, gpu(om)) == pytest.approx(F, abs=1e-14)
+    assert lgf_gpu.functional(Ug, gpu(g)) == pytest.approx(F, abs=1e-14)
+    assert lgf_gpu.plaquette(Ug) == pytest.approx(P, abs=1e-14)
