@@ -5,7 +5,7 @@
 // wavefront's loads of the six entries share their lines) instead of packing
 // them first: a packed copy costs 177 us at 32^4, as much as reading the links
 // twice.  At 32^4 (604 MB of link lines, 123 us at the rate of a copy): F 113
-// us, F and theta 150, the plaquette 287 (pack, divergence and reduction were
+// us, F and theta 150, the plaquette 235 (pack, divergence and reduction were
 // 281, pack and plaquette 337).  A wave's six loads of a link touch 64 segments
 // each, so a kernel that reads sixteen links per site, like the plaquette's, is
 // held by its address unit; loading a wave's links cooperatively and handing
@@ -289,10 +289,14 @@ __global__ void __launch_bounds__(SITE_BLOCK)
 #pragma unroll
         for (int mu = 0; mu < 4; ++mu) {
             const mat3<double> u = link_at(L, mu, s);
-#pragma unroll
-            for (int nu = mu + 1; nu < 4; ++nu)
+            // one plane's three links at a time: 192 VGPRs against 244 unrolled,
+            // the call at 32^4 248 us against 316 (302 with completed rows)
+#pragma unroll 1
+            for (int nu = mu + 1; nu < 4; ++nu) {
+                const long sn = nu == 1 ? n.p[1] : nu == 2 ? n.p[2] : n.p[3];
                 acc += re_tr_dag(mat_mul_full(u, link_at(L, nu, n.p[mu])),
-                                 mat_mul_full(link_at(L, nu, s), link_at(L, mu, n.p[nu])));
+                                 mat_mul_full(link_at(L, nu, s), link_at(L, mu, sn)));
+            }
         }
     }
     block_sum2<SITE_BLOCK>(acc, 0.0, partials, blockIdx.x);
