@@ -360,31 +360,41 @@ int read_status(lgf_ctx *c, dev_status &out) {
     return LGF_OK;
 }
 
+// The first divergence of a phase, of the working links in buffer 0.
+template <class T> auto div_of_links(lgf_ctx *c) {
+    return [c](const fin_params &fp) {
+        return launch_div_reduce<T>(c->g, prec<T>::links(c, 0), prec<T>::field(c, 0), c->partials,
+                                    c->status, fp, c->stream);
+    };
+}
+
 // Runs one precision phase on the working links in buffer 0.  On return the
 // current links (FP64) or accumulated transformation (FP32, acc_G) are those
 // after n = st.n sweeps and `st` holds the final state.
-// prepared: the status reset and the first divergence with its stopping test
-// were enqueued by the caller (the mixed hand-over fuses them).
+// first_div: enqueues the first divergence with its stopping test (given the
+// status reset, and the test's parameters).
 //
 // Sweeps go to the stream in batches.  The last stopping test of a batch
 // writes the state to a pinned host slot (two slots, alternating, each with an
 // event), and the next batch is enqueued before the host waits for the
-// previous one's state, so the device does not idle while the host decides
-// (nor before the first batch, whose sweeps do nothing where the links are
-// fixed already, nor after the last): a solve
-// sizes each batch from the contraction rate last observed, counting the
+// previous one's state, so the device does not idle while the host decides: a
+// solve sizes each batch from the contraction rate last observed, counting the
 // sweeps still in flight; once the stopping test has fired, sweeps still in
 // flight find the device flag set and return at once.  A fixed count of
 // sweeps (tol <= 0) goes in batches of 64.
-template <class T>
+//
+// A solve enqueues `ahead` sweeps before it looks at the first divergence's
+// state: none where that may well end the phase, as links that are fixed
+// already must not pay for empty sweeps (the call at 8^4 52 us; 62 with one
+// sweep ahead of the look, 167 with two batches of four).  Whole solves take the
+// same either way (8^4 650 to 690 us, 16^4 mixed 1410 to 1420).
+template <class T, class FirstDiv>
 int run_phase(lgf_ctx *c, double alpha, double tol, int max_iter, int hist_base, dev_status &st,
-              int stall = 0, bool prepared = false) {
-    if (!prepared) {
-        HIPCHK(c, launch_status_reset(c->status, hist_base, c->stream));
-        HIPCHK(c, launch_div_reduce<T>(c->g, prec<T>::links(c, 0), prec<T>::field(c, 0),
-                                       c->partials, c->status,
-                                       finp(c, true, tol, max_iter, 0, stall), c->stream));
-    }
+              FirstDiv first_div, int stall = 0, int ahead = 0) {
+    HIPCHK(c, launch_status_reset(c->status, hist_base, c->stream));
+    fin_params fp0 = finp(c, true, tol, max_iter, 0, stall);
+    if (tol > 0) fp0.host = c->status_host;
+    HIPCHK(c, first_div(fp0));
     const T half_alpha = (T)(0.5 * alpha);
     c->half_alpha = 0.5 * alpha;
     const fin_params fp = finp(c, true, tol, max_iter, 1, stall);
@@ -423,6 +433,17 @@ int run_phase(lgf_ctx *c, double alpha, double tol, int max_iter, int hist_base,
         return LGF_OK;
     };
     int queued = 0, observed = 0;  // batches enqueued / whose status was read
+    if (tol > 0) {
+        if ((ahead = std::min(ahead, max_iter)) > 0) {
+            HIPCHK(c, hipEventRecord(c->batch_ev[1], c->stream));
+            if ((rc = enqueue_batch(ahead, 0))) return rc;
+            ++queued;
+            HIPCHK(c, hipEventSynchronize(c->batch_ev[1]));
+        } else {
+            HIPCHK(c, hipStreamSynchronize(c->stream));
+        }
+        st = c->status_host[0];
+    }
     while (!st.done) {
         // keep two batches in flight: enqueue the next one (at least one
         // sweep, so the device is never idle before the stop) unless every
@@ -816,7 +837,8 @@ static int solve(lgf_ctx *c, double *U, double alpha, double tol, int max_iter, 
         const double tol32 = std::max(tol, c->theta_switch);
         // the FP32 phase also ends when theta stops reaching new minima (its
         // rounding floor lies above the hand-over threshold)
-        rc = run_phase<float>(c, alpha, tol32, max_iter, 0, st, FP32_STALL_SWEEPS);
+        rc = run_phase<float>(c, alpha, tol32, max_iter, 0, st, div_of_links<float>(c),
+                              FP32_STALL_SWEEPS);
         if (rc) return rc;
         n32 = st.n;
         code = st.code;
@@ -827,23 +849,25 @@ static int solve(lgf_ctx *c, double *U, double alpha, double tol, int max_iter, 
         // SU(3) fused with the FP64 phase's first divergence
         const bool refine = code == ST_CONVERGED || code == ST_MAXITER || code == ST_STALLED;
         const bool fused = refine && c->g.nc == 3;
-        if (fused) {
-            HIPCHK(c, launch_status_reset(c->status, n32, c->stream));
-            HIPCHK(c, launch_switch_div(c->g, acc_G(c, n32), U, c->L64[0], c->D64[0], c->partials,
-                                        c->status, finp(c, true, tol, max_iter - n32, 0, 0),
-                                        c->stream));
-        } else {
-            HIPCHK(c, launch_switch(c->g, acc_G(c, n32), U, c->L64[0], c->stream));
-        }
+        const auto hand_over = [&](const fin_params &fp) {
+            return launch_switch_div(c->g, acc_G(c, n32), U, c->L64[0], c->D64[0], c->partials,
+                                     c->status, fp, c->stream);
+        };
+        if (!fused) HIPCHK(c, launch_switch(c->g, acc_G(c, n32), U, c->L64[0], c->stream));
         if (refine) {
-            rc = run_phase<double>(c, alpha, tol, max_iter - n32, n32, st, 0, fused);
+            // the FP32 phase left theta between tol and tol32, except where it
+            // found nothing to do or the two are the same
+            const int ahead = n32 > 0 && tol < tol32 ? 4 : 0;
+            rc = fused ? run_phase<double>(c, alpha, tol, max_iter - n32, n32, st, hand_over, 0, ahead)
+                       : run_phase<double>(c, alpha, tol, max_iter - n32, n32, st,
+                                           div_of_links<double>(c), 0, ahead);
             if (rc) return rc;
             n64 = st.n;
             code = st.code;
         }
     } else {
         HIPCHK(c, launch_pack_links<double>(U, c->L64[0], c->g, c->stream));
-        rc = run_phase<double>(c, alpha, tol, max_iter, 0, st);
+        rc = run_phase<double>(c, alpha, tol, max_iter, 0, st, div_of_links<double>(c));
         if (rc) return rc;
         n64 = st.n;
         code = st.code;
@@ -890,7 +914,7 @@ int lgf_iterate(lgf_ctx *c, double *U, double alpha, int n_iter, lgf_result *res
     if (c->precision == LGF_MIXED) {
         HIPCHK(c, launch_pack_links<float>(U, c->L32[0], c->g, c->stream));
         if (c->g.nc == 2) HIPCHK(c, launch_g_identity(c->G32, c->g, c->stream));
-        rc = run_phase<float>(c, alpha, 0.0, n_iter, 0, st);
+        rc = run_phase<float>(c, alpha, 0.0, n_iter, 0, st, div_of_links<float>(c));
         if (rc) return rc;
         n32 = st.n;
         if (n32 == 0 && c->g.nc == 3)
@@ -898,7 +922,7 @@ int lgf_iterate(lgf_ctx *c, double *U, double alpha, int n_iter, lgf_result *res
         HIPCHK(c, launch_switch(c->g, acc_G(c, n32), U, c->L64[0], c->stream));
     } else {
         HIPCHK(c, launch_pack_links<double>(U, c->L64[0], c->g, c->stream));
-        rc = run_phase<double>(c, alpha, 0.0, n_iter, 0, st);
+        rc = run_phase<double>(c, alpha, 0.0, n_iter, 0, st, div_of_links<double>(c));
         if (rc) return rc;
         n64 = st.n;
     }

@@ -452,3 +452,32 @@ def test_field32_sweep_is_a_gauge_transformation(lgf_gpu):
     for bad in (16, 0, 128):
         with pytest.raises(lgf_gpu.LgfError):
             c.set_field_precision(bad)
+
+
+@pytest.mark.parametrize("L", [(8, 8, 8, 8), (16, 16, 16, 16)])
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_links_already_fixed_run_no_sweep_kernels(lgf_gpu, L, precision):
+    """Nothing is enqueued past a first divergence that ends the solve: the call
+    takes about the time of no sweeps at all.  The FP64 one does the same work
+    (pack, divergence, unpack), a mixed one twice that with the hand-over in
+    between; eight empty sweeps made the two 2.4 to 3.5 times as long."""
+    import torch
+
+    U, _ = inputs.make_config(L, 0.5, 65)
+    fixed = gpu(U)
+    lgf_gpu.fix(fixed, ALPHA, 1e-12)
+    work = fixed.clone()
+
+    def best(call):
+        times = []
+        for _ in range(30):
+            work.copy_(fixed)
+            torch.cuda.synchronize()
+            r = call()
+            assert r.iterations == 0
+            times.append(r.seconds)
+        return min(times)
+
+    none = best(lambda: lgf_gpu.iterate(work, ALPHA, 0))
+    got = best(lambda: lgf_gpu.fix(work, ALPHA, 1e-12, precision=precision))
+    assert got < (1.5 if precision == "fp64" else 3.0) * none + 5e-6
