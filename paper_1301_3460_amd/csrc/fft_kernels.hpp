@@ -512,7 +512,8 @@ __global__ void __launch_bounds__(rc_max_threads<T>())
     const int SW = Lx + 1, PJ = F * SW;
     const vec2_t<T> *twy = tw_y<T>(g, tw);
     vec2_t<T> *p = D + (long)f * g.S + (long)blockIdx.x * Lxy + x;
-    if (!tiles_first(g) && status->done) return;
+    // a launch that takes the stopping test along passes the state on in any case
+    if (!tiles_first(g) && !fold.fp.enabled && status->done) return;
     cpx<T> a[NY];
 #pragma unroll
     for (int y = 0; y < NY; ++y) a[y] = ld<T>(p + (long)y * Lx);
