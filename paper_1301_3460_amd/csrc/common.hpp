@@ -145,47 +145,59 @@ __device__ __forceinline__ void fixed_order_sum(const double *__restrict__ parti
     B = sb[0];
 }
 
-// The same without a block-wide tree: lane l of a wave adds pairs l, l + n, ...
-// (n lanes), then the lanes are added pairwise.  Blocks of whole waves do it in
-// every wave, without LDS or barriers; other blocks in their first wave.  For
-// a few hundred pairs; the same value in every thread of every block of a
-// launch.
+// The same without a block-wide tree: lane l of 64 adds pairs l, l + 64, ...,
+// then the lanes are added pairwise, in every wave, without LDS or barriers.
+// For a few hundred pairs; the same bits in every thread of every block,
+// whatever its size: the stopping test of a sweep is taken by kernels of
+// different block sizes.  ODD_BLOCKS: also in blocks that are no multiple of a
+// wave; their first wave does it, or, below 64 threads, every thread stands for
+// several lanes, in LDS.
+template <bool ODD_BLOCKS = false>
 __device__ __forceinline__ void wave_sum(const double *__restrict__ partials, int nparts, double &A,
                                          double &B) {
     const double2 *p2 = reinterpret_cast<const double2 *>(partials);
-    const int lane = threadIdx.x & 63;
-    const bool whole = blockDim.x % 64 == 0;
-    const int n = whole ? 64 : min(64u, blockDim.x);
-    double a = 0, b = 0;
-    if (whole || threadIdx.x < 64) {
-        for (int i = lane; i < nparts; i += n) {
+    auto lane_sum = [&](int lane) {
+        double2 r = make_double2(0, 0);
+        for (int i = lane; i < nparts; i += 64) {
             const double2 v = p2[i];
-            a += v.x;
-            b += v.y;
+            r.x += v.x;
+            r.y += v.y;
         }
+        return r;
+    };
+    const bool whole = !ODD_BLOCKS || blockDim.x % 64 == 0;
+    double2 r = make_double2(0, 0);
+    if (whole || (blockDim.x > 64 && threadIdx.x < 64)) {
+        r = lane_sum(threadIdx.x & 63);
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) {
-            const double u = __shfl_down(a, off), v = __shfl_down(b, off);
-            if (lane + off < n) {
-                a += u;
-                b += v;
+            r.x += __shfl_down(r.x, off);
+            r.y += __shfl_down(r.y, off);
+        }
+        r.x = __shfl(r.x, 0);
+        r.y = __shfl(r.y, 0);
+    }
+    if constexpr (ODD_BLOCKS) {
+        if (!whole) {
+            __shared__ double2 v[64];
+            if (blockDim.x > 64) {
+                if (threadIdx.x == 0) v[0] = r;
+            } else {
+                for (int l = threadIdx.x; l < 64; l += blockDim.x) v[l] = lane_sum(l);
+                for (int off = 32; off > 0; off >>= 1) {
+                    __syncthreads();
+                    for (int l = threadIdx.x; l < off; l += blockDim.x) {
+                        v[l].x += v[l + off].x;
+                        v[l].y += v[l + off].y;
+                    }
+                }
             }
+            __syncthreads();
+            r = v[0];
         }
-        a = __shfl(a, 0);
-        b = __shfl(b, 0);
     }
-    if (!whole && blockDim.x > 64) {
-        __shared__ double ab[2];
-        if (threadIdx.x == 0) {
-            ab[0] = a;
-            ab[1] = b;
-        }
-        __syncthreads();
-        a = ab[0];
-        b = ab[1];
-    }
-    A = a;
-    B = b;
+    A = r.x;
+    B = r.y;
 }
 
 // The state after a sweep whose partials sum to A and B: F = A normF, theta =
@@ -231,6 +243,7 @@ __device__ __forceinline__ dev_status next_state(double A, double B, dev_status 
 // The start of a sweep's first kernel: whether the sweeps are over, with the
 // stopping test of the sweep before if fold asks for it (every wave sums the
 // partials; the grid's first thread writes the state).
+template <bool ODD_BLOCKS = false>
 __device__ __forceinline__ bool sweeps_over(const dev_status *__restrict__ status,
                                             const fold_args &fold) {
     if (!fold.fp.enabled) return status->done != 0;
@@ -241,7 +254,7 @@ __device__ __forceinline__ bool sweeps_over(const dev_status *__restrict__ statu
         return true;
     }
     double A, B;
-    wave_sum(fold.partials, fold.nparts, A, B);
+    wave_sum<ODD_BLOCKS>(fold.partials, fold.nparts, A, B);
     const dev_status nx = next_state(A, B, st, fold.fp, first);
     if (first) *fold.out = nx;
     return nx.done != 0;

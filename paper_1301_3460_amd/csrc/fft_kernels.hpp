@@ -517,7 +517,7 @@ __global__ void __launch_bounds__(rc_max_threads<T>())
     cpx<T> a[NY];
 #pragma unroll
     for (int y = 0; y < NY; ++y) a[y] = ld<T>(p + (long)y * Lx);
-    if (DIR < 0 ? sweeps_over(status, fold) : status->done != 0) return discard(a);
+    if (DIR < 0 ? sweeps_over<true>(status, fold) : status->done != 0) return discard(a);
     auto base = [F, SW, PJ](int c) { return (c / F) * PJ + (c % F) * SW; };  // c = fl + F*j
     auto col = [&](int, int C) { col_fft_small<DIR, T>(Lx, lds, F * C, 1, base, tw); };
     if (DIR < 0) {

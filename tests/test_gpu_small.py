@@ -73,3 +73,24 @@ def test_max_iter_ends_inside_a_batch(lgf_gpu, L):
         r = lgf_gpu.fix(Ug, ALPHA, 1e-15, max_iter=k)
         assert r.status == lgf_gpu.LGF_NOT_CONVERGED and r.iterations == k
         assert np.max(np.abs(cpu(Ug) - oracle.iterate(U, ALPHA, k))) < k * 1e-13
+
+
+# register-column planes of fewer than 64 threads (4 x 12; SU(2) 2 x 27 and, with
+# most lanes of the sum missing, 2 x 6), of one wavefront and of two, and the
+# one-block transform
+@pytest.mark.parametrize("L,nc", [((12, 18, 9, 12), 3), ((27, 16, 12, 8), 2), ((6, 16, 16, 16), 2),
+                                  ((16, 16, 8, 9), 3), ((32, 8, 8, 8), 3), ((8, 8, 8, 4), 3)])
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_history_does_not_depend_on_the_batches(lgf_gpu, L, nc, precision):
+    """A sweep's F and theta are the same bits whether its stopping test had a
+    kernel of its own (the last sweep of a call) or rode along."""
+    make = inputs.make_config if nc == 3 else inputs.make_config_su2
+    U, _ = make(L, 0.5, 600 + sum(L))
+    hist = []
+    for n in (6, 1, 2, 3, 4, 5):
+        Ug = gpu(U)
+        lgf_gpu.iterate(Ug, ALPHA, n, precision=precision)
+        hist.append(lgf_gpu._ctx(Ug, precision).history())
+    for F, T in hist[1:]:
+        assert np.array_equal(F, hist[0][0][:len(F)])
+        assert np.array_equal(T, hist[0][1][:len(T)])
