@@ -232,7 +232,12 @@ int lgf_history(lgf_ctx *ctx, double *F, double *theta, int cap, int *count);
  * recorded between the launches of every sweep, all sweeps are enqueued
  * before one synchronisation, and kernel_ms[k] receives the mean duration in
  * milliseconds of: 0 (x,y) forward FFT, 1 (z,t) FFT + scaling + inverse,
- * 2 (x,y) inverse FFT, 3 update + next divergence, 4 finalize. */
+ * 2 (x,y) inverse FFT, 3 update + next divergence, 4 finalize.  The kernels are
+ * those of lgf_fix and lgf_iterate, and a part that a sweep does not launch
+ * counts 0: where one block transforms a field (up to 2048 sites) 0 is the whole
+ * transform; where the stopping test rides along with the next sweep's first
+ * kernel (small lattices) it counts in 0, and 4 is only the last sweep's; without
+ * the acceleration there are no transforms. */
 int lgf_profile(lgf_ctx *ctx, const double *U, double alpha, int n_iter, double *kernel_ms);
 
 /* For callers that cannot allocate device memory (code under HIP graph

@@ -302,12 +302,20 @@ template <class T> bool use_fold(const lgf_ctx *c) {
            (use_small<T>(c) || fft_xy_folds(field32<T>(c) ? c->plan32 : c->plan64));
 }
 
+// Parts of a sweep as lgf_profile reports them.
+enum sweep_part { PART_XY, PART_ZT, PART_XY_INV, PART_UPDATE, PART_FINALIZE, PARTS };
+
+struct no_marks {
+    hipError_t operator()(sweep_part) const { return hipSuccess; }
+};
+
 // Sweep n (counted from the phase's first, 0) from links/field buffer n & 1
 // into the other one.  first, last: the batch's first sweep, and its last,
-// which always has its own stopping test.
-template <class T>
+// which always has its own stopping test.  mark(part): called after the
+// launches of each part the sweep has.
+template <class T, class Mark = no_marks>
 hipError_t enqueue_sweep(lgf_ctx *c, int n, T half_alpha, const fin_params &fp, bool first,
-                         bool last) {
+                         bool last, Mark mark = {}) {
     using P = prec<T>;
     hipError_t e;
     const int cur = n & 1;
@@ -328,28 +336,35 @@ hipError_t enqueue_sweep(lgf_ctx *c, int n, T half_alpha, const fin_params &fp, 
                                            fa, c->stream)
                 : launch_fft4_small<double>(c->g, D, c->tw64, c->pt64, k, c->small64, before, fa,
                                             c->stream);
-        if (e != hipSuccess) return e;
+        if (e != hipSuccess || (e = mark(PART_XY)) != hipSuccess) return e;
         // G <- g G of the sweeps that keep U0 and G
         if (std::is_same<T, float>::value && c->g.nc == 3) {
             e = launch_gauge_acc<float, float>(c->g, D, n ? acc_G(c, cur) : nullptr,
                                                acc_G(c, cur ^ 1), c->half_alpha, c->exact_exp,
                                                c->status, c->stream);
-            if (e != hipSuccess) return e;
+            if (e != hipSuccess || (e = mark(PART_XY_INV)) != hipSuccess) return e;
         }
     } else {
         int pass = 0;
         if (fa.fp.enabled) {
             e = f32 ? launch_fft_xy<float>(c->g, D, -1, c->tw32, c->plan32, before, c->stream, fa)
                     : launch_fft_xy<double>(c->g, D, -1, c->tw64, c->plan64, before, c->stream, fa);
-            if (e != hipSuccess) return e;
+            if (e != hipSuccess || (e = mark(PART_XY)) != hipSuccess) return e;
             pass = 1;
         }
-        for (; pass < 3; ++pass)
+        // without the acceleration only G <- g G of sweeps that keep U0 remains
+        const bool acc = std::is_same<T, float>::value ? c->g.nc == 3 : c->g.keeps_u0();
+        for (; pass < 3; ++pass) {
             if ((e = sweep_pass<T>(c, n, D, pass)) != hipSuccess) return e;
+            if ((c->accelerate || (acc && pass == 2)) &&
+                (e = mark((sweep_part)(PART_XY + pass))) != hipSuccess)
+                return e;
+        }
     }
-    fin_params test = fp;
-    if (fold && !last) test.enabled = 0;
-    return sweep_update<T>(c, cur, D, half_alpha, test);
+    e = sweep_update<T>(c, cur, D, half_alpha, finp(c, false));
+    if (e != hipSuccess || (e = mark(PART_UPDATE)) != hipSuccess || (fold && !last)) return e;
+    e = launch_finalize(c->partials, update_parts<T>(c), c->status, fp, c->stream);
+    return e == hipSuccess ? mark(PART_FINALIZE) : e;
 }
 
 int read_status(lgf_ctx *c, dev_status &out) {
@@ -558,42 +573,29 @@ int profile_impl(lgf_ctx *c, const double *U, double alpha, int n, double *ms) {
     HIPCHK(c, launch_status_reset(c->status, 0, c->stream));
     HIPCHK(c, launch_div_reduce<T>(c->g, P::links(c, 0), P::field(c, 0), c->partials, c->status,
                                    finp(c, true, 0.0, n + 1, 0), c->stream));
-    std::vector<hipEvent_t> ev((size_t)n * 6);
+    // one event before the sweeps and one after each part of each
+    std::vector<hipEvent_t> ev((size_t)n * PARTS + 1);
     for (auto &e : ev) HIPCHK(c, hipEventCreate(&e));
+    std::vector<sweep_part> parts;
+    parts.reserve((size_t)n * PARTS);
+    auto mark = [&](sweep_part p) {
+        parts.push_back(p);
+        return hipEventRecord(ev[parts.size()], c->stream);
+    };
     const T half_alpha = (T)(0.5 * alpha);
     c->half_alpha = 0.5 * alpha;
-    int rc = LGF_OK;
-    for (int it = 0; it < n && rc == LGF_OK; ++it) {
-        const int cur = it & 1;
-        void *D = P::field(c, cur);
-        hipEvent_t *e = &ev[(size_t)it * 6];
-        hipError_t err = hipSuccess;
-        auto chk = [&](hipError_t x) { if (err == hipSuccess) err = x; };
-        chk(hipEventRecord(e[0], c->stream));
-        chk(sweep_pass<T>(c, it, D, 0));
-        chk(hipEventRecord(e[1], c->stream));
-        chk(sweep_pass<T>(c, it, D, 1));
-        chk(hipEventRecord(e[2], c->stream));
-        chk(sweep_pass<T>(c, it, D, 2));
-        chk(hipEventRecord(e[3], c->stream));
-        chk(sweep_update<T>(c, cur, D, half_alpha, finp(c, false)));
-        chk(hipEventRecord(e[4], c->stream));
-        chk(launch_finalize(c->partials, update_parts<T>(c), c->status, finp(c, true, 0.0, n + 1, 1),
-                            c->stream));
-        chk(hipEventRecord(e[5], c->stream));
-        if (err != hipSuccess) rc = fail(c, LGF_ERR_DEVICE, hipGetErrorString(err));
+    const fin_params fp = finp(c, true, 0.0, n + 1, 1);
+    hipError_t err = hipEventRecord(ev[0], c->stream);
+    for (int it = 0; it < n && err == hipSuccess; ++it)
+        err = enqueue_sweep<T>(c, it, half_alpha, fp, it == 0, it == n - 1, mark);
+    if (err == hipSuccess) err = hipStreamSynchronize(c->stream);
+    for (int k = 0; k < PARTS; ++k) ms[k] = 0;
+    for (size_t i = 0; i < parts.size() && err == hipSuccess; ++i) {
+        float t = 0;
+        err = hipEventElapsedTime(&t, ev[i], ev[i + 1]);
+        ms[parts[i]] += t / n;
     }
-    if (rc == LGF_OK) {
-        hipError_t err = hipStreamSynchronize(c->stream);
-        for (int k = 0; k < 5; ++k) ms[k] = 0;
-        for (int it = 0; it < n && err == hipSuccess; ++it)
-            for (int k = 0; k < 5 && err == hipSuccess; ++k) {
-                float t = 0;
-                err = hipEventElapsedTime(&t, ev[(size_t)it * 6 + k], ev[(size_t)it * 6 + k + 1]);
-                ms[k] += t / n;
-            }
-        if (err != hipSuccess) rc = fail(c, LGF_ERR_DEVICE, hipGetErrorString(err));
-    }
+    const int rc = err == hipSuccess ? LGF_OK : fail(c, LGF_ERR_DEVICE, hipGetErrorString(err));
     for (auto &e : ev) (void)hipEventDestroy(e);
     return rc;
 }

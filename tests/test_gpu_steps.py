@@ -227,3 +227,35 @@ def test_resume_is_bitwise(lgf_gpu):
     b = gpu(cpu(b))
     lgf_gpu.iterate(b, 0.08, 4)
     assert np.array_equal(cpu(a), cpu(b))
+
+
+@pytest.mark.parametrize("L,precision,parts", [
+    ((4, 4, 4, 8), "fp64", ("fft_xy_fwd", "update")),  # one block per field
+    ((4, 4, 4, 8), "mixed", ("fft_xy_fwd", "fft_xy_inv", "update")),  # and G after it
+    ((8, 8, 8, 8), "fp64", ("fft_xy_fwd", "fft_zt", "fft_xy_inv", "update")),
+    ((64, 32, 16, 16), "fp64", ("fft_xy_fwd", "fft_zt", "fft_xy_inv", "update", "finalize")),
+])
+def test_profile_times_the_kernels_of_the_sweep(lgf_gpu, L, precision, parts):
+    """Parts a sweep does not launch count nothing; a stopping test that rides
+    along leaves only that of the last of the 64 sweeps."""
+    Ug = gpu(_config(L, 16))
+    before = Ug.clone()
+    ctx = lgf_gpu.Context(L, precision)
+    ctx.profile(Ug, 0.08, 4)
+    ms = ctx.profile(Ug, 0.08, 64)
+    ctx.close()
+    assert np.array_equal(cpu(Ug), cpu(before))
+    for k in ("fft_xy_fwd", "fft_zt", "fft_xy_inv", "update"):
+        assert (ms[k] > 0) == (k in parts), ms
+    if "finalize" not in parts:
+        assert 0 < ms["finalize"] < ms["update"] / 8, ms
+
+
+@pytest.mark.parametrize("L", [(4, 4, 4, 8), (16, 16, 16, 12)])
+def test_profile_without_transforms(lgf_gpu, L):
+    ctx = lgf_gpu.Context(L, "fp64")
+    ctx.set_acceleration(False)
+    ms = ctx.profile(gpu(_config(L, 17)), 0.08, 16)
+    ctx.close()
+    assert ms["fft_xy_fwd"] == ms["fft_zt"] == 0 and ms["update"] > 0 and ms["finalize"] > 0
+    assert (ms["fft_xy_inv"] > 0) == (L[0] == 16)  # G <- g G where U0 is kept
