@@ -526,6 +526,17 @@ bool alloc_links(lgf_ctx *c) {
     return true;
 }
 
+// g of the exact step, for the FP64 sweeps that store their links (SU(3)); the
+// others form it inside the pass that accumulates G.
+bool ensure_gex(lgf_ctx *c, bool exact) {
+    if (!exact || c->g.nc != 3 || c->g.keeps_u0() || c->Gex) return true;
+    if (hipSetDevice(c->device) == hipSuccess &&
+        hipMalloc((void **)&c->Gex, (size_t)6 * c->g.S * sizeof(double2)) == hipSuccess)
+        return true;
+    c->Gex = nullptr;
+    return false;
+}
+
 int check_ctx(lgf_ctx *c) {
     if (!c) return LGF_ERR_ARG;
     if (!c->L64[0] || !c->L64[1])
@@ -783,7 +794,7 @@ int lgf_set_link_format(lgf_ctx *c, int nreal) {
     if (hipSetDevice(c->device) != hipSuccess || hipStreamSynchronize(c->stream) != hipSuccess)
         return fail(c, LGF_ERR_DEVICE, "device unavailable");
     c->g.lf = nreal;
-    if (!alloc_links(c)) {
+    if (!alloc_links(c) || !ensure_gex(c, c->exact_exp)) {
         c->g.lf = 12;
         (void)alloc_links(c);  // on failure the buffers stay null; check_ctx reports it
         return fail(c, LGF_ERR_OOM, "out of device memory (links)");
@@ -800,13 +811,8 @@ int lgf_set_field_precision(lgf_ctx *c, int bits) {
 
 int lgf_set_exponential(lgf_ctx *c, int exact) {
     if (!c) return LGF_ERR_ARG;
-    if (exact && c->g.nc == 3 && !c->Gex) {
-        if (hipSetDevice(c->device) != hipSuccess ||
-            hipMalloc((void **)&c->Gex, (size_t)6 * c->g.S * sizeof(double2)) != hipSuccess) {
-            c->Gex = nullptr;
-            return fail(c, LGF_ERR_OOM, "out of device memory (exact exponential)");
-        }
-    }
+    if (!ensure_gex(c, exact != 0))
+        return fail(c, LGF_ERR_OOM, "out of device memory (exact exponential)");
     c->exact_exp = exact != 0;
     return LGF_OK;
 }

@@ -96,3 +96,23 @@ def test_resume_to_rounding(lgf_gpu):
                                (64, 32, 16, 12)])
 def test_three_sweeps_shared_links(lgf_gpu, L):
     test_three_sweeps(lgf_gpu, L, {})
+
+
+def test_exact_step_needs_no_memory_of_its_own(lgf_gpu):
+    """G takes the exponential inside the pass that accumulates it; the buffer
+    for it comes with a format whose sweeps store their links."""
+    import torch
+
+    L = (32, 32, 16, 16)
+    U, _ = inputs.make_config(L, 0.5, 902)
+    ctx = lgf_gpu.Context(L, "fp64")
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    ctx.set_exponential(True)
+    assert torch.cuda.mem_get_info()[0] == free
+    a, b = gpu(U), gpu(U)
+    ctx.iterate(a, ALPHA, 2)
+    ctx.set_link_format(18)
+    ctx.iterate(b, ALPHA, 2)
+    ctx.close()
+    assert np.max(np.abs(cpu(a) - cpu(b))) < 3e-13
