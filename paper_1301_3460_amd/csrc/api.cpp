@@ -6,6 +6,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <functional>
 #include <mutex>
 #include <new>
 #include <string>
@@ -545,6 +546,20 @@ int check_ctx(lgf_ctx *c) {
     return LGF_OK;
 }
 
+// Where a kernel that still reads the n_in doubles at `in` may write its n_out
+// doubles of output: `out` itself or, where the two overlap, the second link
+// buffer (48 doubles a site), from which finish_output copies them.
+double *output_of(lgf_ctx *c, double *out, long n_out, const double *in, long n_in) {
+    const bool apart = !in || std::less_equal<const double *>()(out + n_out, in) ||
+                       std::less_equal<const double *>()(in + n_in, out);
+    return apart ? out : reinterpret_cast<double *>(c->L64[1]);
+}
+
+hipError_t finish_output(lgf_ctx *c, double *out, long n_out, const double *written) {
+    if (written == out) return hipSuccess;
+    return hipMemcpyAsync(out, written, n_out * sizeof(double), hipMemcpyDeviceToDevice, c->stream);
+}
+
 // Sums the partials of a measurement into reduce_host and waits for the stream.
 int sum_partials(lgf_ctx *c, double &A, double &B) {
     HIPCHK(c, launch_reduce_only(c->partials, c->nparts, c->reduce_out, c->stream));
@@ -1003,8 +1018,10 @@ int lgf_divergence(lgf_ctx *c, const double *U, double *Delta) {
     if (!U || !Delta) return fail(c, LGF_ERR_ARG, "null argument");
     int rc = check_ctx(c);
     if (rc) return rc;
-    HIPCHK(c, launch_div_aos(c->g, U, reinterpret_cast<double2 *>(Delta), 1, c->partials,
-                             c->stream));
+    const long V = c->g.V;
+    double *to = output_of(c, Delta, 18 * V, U, 72 * V);
+    HIPCHK(c, launch_div_aos(c->g, U, reinterpret_cast<double2 *>(to), 1, c->partials, c->stream));
+    HIPCHK(c, finish_output(c, Delta, 18 * V, to));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     return LGF_OK;
 }
@@ -1080,7 +1097,10 @@ int lgf_functional_omega_grad(lgf_ctx *c, const double *U, const double *omega, 
     if (!U || !omega || !F || !dF) return fail(c, LGF_ERR_ARG, "null argument");
     int rc = check_ctx(c);
     if (rc) return rc;
-    HIPCHK(c, launch_omega_grad(c->g, U, omega, c->L64[0], dF, normF(c), c->partials, c->stream));
+    const long V = c->g.V;
+    double *to = output_of(c, dF, 8 * V, U, 72 * V);
+    HIPCHK(c, launch_omega_grad(c->g, U, omega, c->L64[0], to, normF(c), c->partials, c->stream));
+    HIPCHK(c, finish_output(c, dF, 8 * V, to));
     double A, B;
     rc = sum_partials(c, A, B);
     if (rc) return rc;
@@ -1096,9 +1116,13 @@ int lgf_theta_grad(lgf_ctx *c, const double *U, const double *eps, double *theta
     if (rc) return rc;
     HIPCHK(c, launch_theta_links(c->g, U, eps, c->L64[0], dtheta ? c->D64[0] : nullptr, c->partials,
                                  c->stream));
-    if (dtheta)
-        HIPCHK(c, launch_theta_grad(c->g, U, eps, c->L64[0], c->D64[0], dtheta, normT(c),
-                                    c->stream));
+    if (dtheta) {
+        // with eps the links were copied (L64[0]) before
+        const long V = c->g.V;
+        double *to = output_of(c, dtheta, 32 * V, eps ? nullptr : U, 72 * V);
+        HIPCHK(c, launch_theta_grad(c->g, U, eps, c->L64[0], c->D64[0], to, normT(c), c->stream));
+        HIPCHK(c, finish_output(c, dtheta, 32 * V, to));
+    }
     double A, B;
     rc = sum_partials(c, A, B);
     if (rc) return rc;

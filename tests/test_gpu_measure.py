@@ -96,3 +96,46 @@ def test_unaligned_parameters(lgf_gpu):
     view.copy_(om)
     a, b = lgf_gpu.functional_omega_grad(U, om), lgf_gpu.functional_omega_grad(U, view)
     assert a[0] == b[0] and torch.equal(a[1], b[1])
+
+
+@pytest.mark.parametrize("L", [(8, 8, 8, 8), (27, 9, 4, 6)])
+def test_outputs_over_the_inputs(lgf_gpu, L):
+    """Delta, dF/domega and dtheta/deps written over the links, or over omega or
+    eps, are those written elsewhere (C ABI; the binding allocates them)."""
+    import ctypes
+
+    import torch
+
+    lib = lgf_gpu.load()
+    U = gpu(inputs.make_config(L, 0.5, 91)[0])
+    om = gpu(inputs.random_omega(L, 0.3, 92))
+    eps = gpu(np.random.default_rng(93).normal(0, 0.3, (4,) + inputs.site_shape(L) + (8,)))
+    ctx = lgf_gpu._ctx(U)
+    val = ctypes.c_double()
+    p = lambda t, off=0: ctypes.c_void_p(t.data_ptr() + off)
+    V = int(np.prod(L))
+
+    def written(call, ref, start, off=0):
+        """What call(buffer) leaves at `off` bytes of a copy of `start`."""
+        buf = start.clone()
+        assert call(buf, p(buf, off)) == 0
+        got = torch.view_as_real(buf) if buf.is_complex() else buf
+        flat = got.reshape(-1)[off // 8:off // 8 + ref.numel()]
+        return torch.equal(flat, ref.reshape(-1))
+
+    D = torch.view_as_real(ctx.divergence(U))
+    _, dF = ctx.functional_omega_grad(U, om)
+    _, t0 = ctx.theta_grad(U)
+    _, t1 = ctx.theta_grad(U, eps)
+    for off in (0, 16 * V):
+        assert written(lambda b, o: lib.lgf_divergence(ctx._h, p(b), o), D, U, off)
+        assert written(lambda b, o: lib.lgf_functional_omega_grad(
+            ctx._h, p(b), p(om), ctypes.byref(val), o), dF, U, off)
+        assert written(lambda b, o: lib.lgf_theta_grad(
+            ctx._h, p(b), None, ctypes.byref(val), o), t0, U, off)
+        assert written(lambda b, o: lib.lgf_theta_grad(
+            ctx._h, p(b), p(eps), ctypes.byref(val), o), t1, U, off)
+    assert written(lambda b, o: lib.lgf_functional_omega_grad(
+        ctx._h, p(U), p(b), ctypes.byref(val), o), dF, om)
+    assert written(lambda b, o: lib.lgf_theta_grad(
+        ctx._h, p(U), p(b), ctypes.byref(val), o), t1, eps)
