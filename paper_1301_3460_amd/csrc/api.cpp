@@ -763,11 +763,8 @@ int lgf_create_group(lgf_ctx **out, const int L[4], int nc, int precision, void 
     // best effort: a launch that still exceeds the limit reports its own error
     fft_set_max_lds<double>(c->g, c->plan64);
     fft_set_max_lds<float>(c->g, c->plan32);
-    update_set_max_lds();
     c->small64 = plan_small<double>(c->g, c->plan64);
     c->small32 = plan_small<float>(c->g, c->plan32);
-    small_set_max_lds<double>(c->small64);
-    small_set_max_lds<float>(c->small32);
     if (e != hipSuccess) {
         std::string m = std::string("initialisation failed: ") + hipGetErrorString(e);
         lgf_destroy(c);

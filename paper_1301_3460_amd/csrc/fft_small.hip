@@ -82,11 +82,15 @@ __global__ void __launch_bounds__(NTHR)
 }
 
 constexpr int SMALL_THREADS_16 = 1024, SMALL_THREADS_32 = 512;
+// rows of two sites pad the most, and no four extents of so few sites add up to
+// more than 256 + 2 + 2 + 2 twiddles
+static_assert((SMALL_MAX_SITES / 2 * 3 + 262) * sizeof(double2) <= 64 * 1024,
+              "LDS of a field beyond what a launch gets without an attribute");
 
 template <class T> small_plan plan_small(const geom &g, const fft_plan &p) {
     small_plan s;
     const size_t lds = ((size_t)(g.V / g.Lx) * (g.Lx + 1) + g.Lx + g.Ly + g.Lz + g.Lt) * sizeof(vec2_t<T>);
-    if (g.V > SMALL_MAX_SITES || lds > SMALL_LDS_MAX) return s;
+    if (g.V > SMALL_MAX_SITES) return s;
     s.on = true;
     s.lds = lds;
     s.rmax = std::max(std::max(fft_tier(g.Lx), fft_tier(g.Ly)), std::max(fft_tier(g.Lz), fft_tier(g.Lt)));
@@ -107,15 +111,6 @@ template <class T> small_plan plan_small(const geom &g, const fft_plan &p) {
     return s;
 }
 
-template <class T> void small_set_max_lds(const small_plan &s) {
-    if (!s.on) return;
-    auto set = [&](const void *f) {
-        (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)s.lds);
-    };
-    set(reinterpret_cast<const void *>(&k_fft4_small<T, 16, SMALL_THREADS_16>));
-    set(reinterpret_cast<const void *>(&k_fft4_small<T, 32, SMALL_THREADS_32>));
-}
-
 template <class T>
 hipError_t launch_fft4_small(const geom &g, void *D, const void *tw, const T *ptab, T p2max_over_V,
                              const small_plan &sp, const dev_status *status, const fold_args &fold,
@@ -134,7 +129,6 @@ hipError_t launch_fft4_small(const geom &g, void *D, const void *tw, const T *pt
 
 #define LGF_SMALL(T)                                                                              \
     template small_plan plan_small<T>(const geom &, const fft_plan &);                            \
-    template void small_set_max_lds<T>(const small_plan &);                                       \
     template hipError_t launch_fft4_small<T>(const geom &, void *, const void *, const T *, T,    \
                                              const small_plan &, const dev_status *,              \
                                              const fold_args &, hipStream_t);

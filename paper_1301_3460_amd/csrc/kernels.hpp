@@ -141,7 +141,9 @@ hipError_t launch_update_u0(const geom &g, const void *U0, const void *G, void *
 // (UPDATE_DIRS_MAX_SITES, 12 reals, SU(3)): launch_update<double> with a lane
 // per link, update_dirs_parts pairs of partials.
 // 8^4 9.7 -> 5.9 us, 16 x 8^3 10.5 -> 6.7, 64 x 6 x 6 x 4 11.5 -> 8; it forms
-// every g eight times, and at 12 x 16 x 12 x 8 (18432 sites) the gain is gone.
+// every g eight times, and the gain falls to 1.2 to 1.7 us at 12 x 16 x 12 x 8 and
+// 9^3 x 27.  The limit is FOLD_MAX_PARTS blocks of 32 sites: at 12^4, the next
+// extents, its partials would no longer ride along, which costs more than that.
 constexpr long UPDATE_DIRS_MAX_SITES = 20480;
 int update_dirs_parts(const geom &g);
 hipError_t launch_update_dirs(const geom &g, const void *Lin, void *Lout, const void *LD,
@@ -214,7 +216,6 @@ bool fft_plan_fits(const fft_plan &p);
 template <class T> void fft_set_max_lds(const geom &g, const fft_plan &p);
 // LDS limit of the FP32 update that shares links through LDS (once per process
 // and device is enough; repeating it is harmless)
-void update_set_max_lds();
 // Twiddle tables: one buffer per real type with the axis tables
 // exp(-2 pi i j / L_mu), j < L_mu, of x, y, z and t one after the other.
 // The stopping test of the sweep before, taken along by the first kernel of
@@ -249,9 +250,7 @@ struct small_plan {
 // passes: 4^4 25.8 -> 20.6 us, 9 x 4 x 6 x 8 30 -> 23, but 8^4 24.6 -> 26.7 and
 // 16 x 8^3 26.4 -> 34.7.
 constexpr long SMALL_MAX_SITES = 2048;
-constexpr size_t SMALL_LDS_MAX = 144 * 1024;
 template <class T> small_plan plan_small(const geom &g, const fft_plan &p);
-template <class T> void small_set_max_lds(const small_plan &s);
 // The round trip of all fields and the stopping test `fold` of the sweep before
 template <class T>
 hipError_t launch_fft4_small(const geom &g, void *D, const void *tw, const T *ptab, T p2max_over_V,

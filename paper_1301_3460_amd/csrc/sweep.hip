@@ -566,14 +566,17 @@ __global__ void __launch_bounds__(SITE_BLOCK)
 // per-link projections change the rounding order of the sums, not the
 // quantities.  Partial sums go out per group of SITE_BLOCK threads, so the
 // finalize reads the same number of partials as after k_update.
-// Blocks of 128 xy-sites x 4 t (512 threads, 64 KB of LDS) let two blocks
-// share a compute unit, so that one block's loads overlap the other's
-// arithmetic: 73 against 82 us at 32^4 and 797 against 828 us at 48^3 x 96
-// for one block of 256 x 4 (or 256 x 2: 74 / 848 us; 128 x 2: 73 / 855 us).
+// Blocks of 128 xy-sites x 4 t (512 threads, 48 KB of LDS) let two blocks
+// share a compute unit (their registers allow no third), so that one block's
+// loads overlap the other's arithmetic: with the z links' P in LDS as well (64
+// KB) 73 against 82 us at 32^4 and 797 against 828 us at 48^3 x 96 for one block
+// of 256 x 4 (or 256 x 2: 74 / 848 us; 128 x 2: 73 / 855 us).
 // Lattices with less than one such block per compute unit take blocks of 64 x 4.
 constexpr int UPDS_T = 4;
 constexpr long UPDS_SPLIT_SITES = 131072;
 template <class T, int XY> constexpr size_t upds_lds() { return (size_t)8 * 3 * XY * UPDS_T * sizeof(T); }
+static_assert(upds_lds<float, 128>() == 48 * 1024 && upds_lds<double, 64>() == 48 * 1024,
+              "the update is launched without raising the LDS limit of 64 KB");
 
 // FP32: the loads of U0's x, y and t links (each read once by its own block)
 // are streaming where the sweep's data do not fit the 256 MB last-level cache
@@ -753,11 +756,6 @@ __global__ void __launch_bounds__(UPDS_XY * UPDS_T)
     st_stream<TF>(Dout + 3 * S + s, cvt<TF>(f3));
     group_sum2<UPDS_THREADS, SITE_BLOCK>((double)tr, (double)th, partials,
                                          blockIdx.x * (UPDS_THREADS / SITE_BLOCK));
-}
-
-void update_set_max_lds() {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_update_shared<float, float, 128, false>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)upds_lds<float, 128>());
 }
 
 // reorder 4 fields between natural index order and transform-position order

@@ -94,3 +94,17 @@ def test_history_does_not_depend_on_the_batches(lgf_gpu, L, nc, precision):
     for F, T in hist[1:]:
         assert np.array_equal(F, hist[0][0][:len(F)])
         assert np.array_equal(T, hist[0][1][:len(T)])
+
+
+# the one-block transform, with 49 KB of LDS at the second shape
+@pytest.mark.parametrize("L", [(8, 8, 8, 4), (2, 4, 16, 16), (9, 3, 2, 6)])
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("nc", [3, 2])
+def test_runs_are_bitwise_equal(lgf_gpu, L, precision, nc):
+    make = inputs.make_config if nc == 3 else inputs.make_config_su2
+    U, _ = make(L, 0.5, 650 + sum(L))
+    a, b = gpu(U), gpu(U)
+    ra = lgf_gpu.iterate(a, ALPHA, 9, precision=precision)
+    rb = lgf_gpu.iterate(b, ALPHA, 9, precision=precision)
+    assert np.array_equal(cpu(a), cpu(b))
+    assert ra.F == rb.F and ra.theta == rb.theta

@@ -116,3 +116,26 @@ def test_exact_step_needs_no_memory_of_its_own(lgf_gpu):
     ctx.iterate(b, ALPHA, 2)
     ctx.close()
     assert np.max(np.abs(cpu(a) - cpu(b))) < 3e-13
+
+
+# one shape per path whose blocks exchange data through LDS: the update of each
+# thread's own links after blocks that end in part of a wave, the FP64 and FP32
+# updates that share links, (x,y) planes of the four fields in LDS
+@pytest.mark.parametrize("L", [(27, 9, 16, 18), (48, 32, 8, 48), (64, 12, 8, 8)])
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_runs_are_bitwise_equal(lgf_gpu, L, precision):
+    U, _ = inputs.make_config(L, 0.5, 950 + sum(L))
+    a, b = gpu(U), gpu(U)
+    ra = lgf_gpu.iterate(a, ALPHA, 4, precision=precision)
+    rb = lgf_gpu.iterate(b, ALPHA, 4, precision=precision)
+    assert np.array_equal(cpu(a), cpu(b))
+    assert ra.F == rb.F and ra.theta == rb.theta
+
+
+@pytest.mark.parametrize("kw", [{"exact_exp": True}, {"accelerate": False}])
+def test_shared_links_step_options(lgf_gpu, kw):
+    test_three_sweeps(lgf_gpu, (48, 32, 8, 48), kw)
+
+
+def test_shared_links_fp32_field(lgf_gpu):
+    test_fp32_field(lgf_gpu, (64, 32, 16, 16))
