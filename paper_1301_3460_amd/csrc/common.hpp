@@ -156,12 +156,18 @@ template <bool ODD_BLOCKS = false>
 __device__ __forceinline__ void wave_sum(const double *__restrict__ partials, int nparts, double &A,
                                          double &B) {
     const double2 *p2 = reinterpret_cast<const double2 *>(partials);
+    // four loads in flight; beyond the last pair +0 is added, which changes no sum
     auto lane_sum = [&](int lane) {
         double2 r = make_double2(0, 0);
-        for (int i = lane; i < nparts; i += 64) {
-            const double2 v = p2[i];
-            r.x += v.x;
-            r.y += v.y;
+        for (int i = lane; i < nparts; i += 256) {
+            double2 v[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v[k] = p2[min(i + 64 * k, nparts - 1)];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                r.x += i + 64 * k < nparts ? v[k].x : 0.0;
+                r.y += i + 64 * k < nparts ? v[k].y : 0.0;
+            }
         }
         return r;
     };
