@@ -259,3 +259,16 @@ def test_profile_without_transforms(lgf_gpu, L):
     ctx.close()
     assert ms["fft_xy_fwd"] == ms["fft_zt"] == 0 and ms["update"] > 0 and ms["finalize"] > 0
     assert (ms["fft_xy_inv"] > 0) == (L[0] == 16)  # G <- g G where U0 is kept
+
+
+@pytest.mark.parametrize("L,nc,kw", [((16, 16, 16, 9), 3, {}), ((8, 8, 8, 4), 3, {"exact_exp": True}),
+                                     ((16, 16, 16, 12), 3, {"link_format": 18}),
+                                     ((16, 16, 16, 16), 2, {}), ((32, 32, 16, 16), 2, {})])
+def test_split_calls_are_bitwise_where_links_are_stored(lgf_gpu, L, nc, kw):
+    make = inputs.make_config if nc == 3 else inputs.make_config_su2
+    U, _ = make(L, 0.5, 18)
+    a, b = gpu(U), gpu(U)
+    lgf_gpu.iterate(a, 0.08, 7, **kw)
+    lgf_gpu.iterate(b, 0.08, 3, **kw)
+    lgf_gpu.iterate(b, 0.08, 4, **kw)
+    assert np.array_equal(cpu(a), cpu(b))
