@@ -99,12 +99,17 @@ inline geom make_geom(const int L[4], int nc) {
 
 // FP64 sweeps of 12-real SU(3) links keep U0 and G from this volume on.  Such
 // a sweep moves 1056 bytes per site (update 544, inverse pass with G 256, the
-// other two passes 128 each) where one that stores its links moves 1280, but
-// its inverse pass also reads and writes G: per sweep, stored links against
-// U0 and G, 48.0 / 49.3 us at 18^2 x 12 x 9 (34992 sites), 53.0 / 50.0 at 16^4,
+// other two passes 128 each; 1184 where G has a kernel of its own after the
+// inverse pass) where one that stores its links moves 1280, but its inverse
+// pass also reads and writes G: per sweep, stored links against U0 and G,
+// 48.0 / 49.3 us at 18^2 x 12 x 9 (34992 sites), 53.0 / 50.0 at 16^4,
 // 74.8 / 66.6 at 16^3 x 32, 135 / 109 at 24^4, and with the update that shares
 // links through LDS 290 / 257 at 32^4 and 3370 / 3207 at 48^3 x 96, whose inverse
-// (x,t) pass leaves G to a kernel of its own.
+// (x,t) pass leaves G to a kernel of its own.  The links are formed once more
+// when they are written back (32^4 216 against 163 us), but the first sweep reads
+// no G, so that the rule needs no look at the number of sweeps: a call of one
+// sweep takes 114 us against 125 at 16^4, 363 / 378 at 24^4, 1012 / 1017 at 32^4
+// and 11106 / 11151 at 48^3 x 96.
 constexpr long KEEP_U0_MIN_SITES = 49152;
 inline bool geom::keeps_u0() const { return nc == 3 && lf == 12 && V >= KEEP_U0_MIN_SITES; }
 
@@ -234,9 +239,8 @@ hipError_t launch_fft_xy(const geom &g, void *D, int dir, const void *tw, const 
                          const dev_status *status, hipStream_t st, const fold_args &fold = {});
 bool fft_xy_folds(const fft_plan &pl);
 // pairs of partials up to which it rides along and the test's own kernel is one
-// wave: each wave then reads at most ten pairs per lane (8^4: 27 against 23 us
-// per sweep with the tile loads under the state's latency; the kernel of its
-// own took 3.1 us there and 4.0 at 16^4)
+// wave: each wave then reads at most ten pairs per lane, under the latency of
+// its tile's loads, where the test's own kernel took 3.1 us at 8^4 and 4.0 at 16^4
 constexpr int FOLD_MAX_PARTS = 640;
 // Small lattices: the whole transform of a field in one block (fft_small.hip)
 struct small_plan {

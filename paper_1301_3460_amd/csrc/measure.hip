@@ -4,10 +4,10 @@
 // are (complex128 [4][V][3][3], rows 0,1 of each link; 144 bytes apart, and a
 // wavefront's loads of the six entries share their lines) instead of packing
 // them first: a packed copy costs 177 us at 32^4, as much as reading the links
-// twice.  At 32^4 (604 MB of link lines, 123 us at the rate of a copy): F 113
-// us, F and theta 150, the plaquette 235 (pack, divergence and reduction were
+// twice.  At 32^4 (604 MB of link lines, 123 us at the rate of a copy): F 108
+// us, F and theta 152, the plaquette 233 (pack, divergence and reduction were
 // 281, pack and plaquette 337).  A wave's six loads of a link touch 64 segments
-// each, so a kernel that reads sixteen links per site, like the plaquette's, is
+// each, so a kernel that reads 22 links per site, like the plaquette's, is
 // held by its address unit; loading a wave's links cooperatively and handing
 // them out through LDS was slower all the same (plaquette 676 us, theta 379).
 #include "common.hpp"

@@ -590,8 +590,8 @@ inline bool upds_stream(const geom &g) {
 
 // FP64 (sweeps that keep U0 and G): blocks of 64 x 4, two per compute unit, two
 // waves per SIMD, where k_update_u0's neighbour reads leave L2: 32^4 147 -> 136
-// us, 24^3 x 48 98 -> 94, 48^3 x 96 1531 -> 1512, but 16^2 x 32^2 32.1 -> 34.3
-// and 24^4 43.9 -> 47.6.  Streaming loads do not help here (136 -> 140).
+// us, 24^3 x 48 98 -> 94, 48^3 x 96 1531 -> 1512, but 16^2 x 32^2 32.5 -> 33.4
+// and 24^4 44.5 -> 47.3.  Streaming loads do not help here (136 -> 140).
 inline bool update_shared64_ok(const geom &g) {
     return g.keeps_u0() && g.V >= 524288 && (long)g.Lx * g.Ly % 64 == 0 && g.Lt % UPDS_T == 0;
 }
